@@ -4,6 +4,9 @@
 // C[M, N] = A[M, K] B[N, K]^T with A the packed activations (bf16, K contiguous) and B a
 // weight matrix in [out, in] layout (bf16, K contiguous), float32 accumulation.
 //
+// Batches whose 256 x 256 tiles are too few for the CUs, or that leave a last round nearly empty,
+// go to the smaller tiles of k_gemm_tiles.hip in whole or in part (gemm_split below).
+//
 // Tiling: one 256-thread workgroup (4 wavefronts, one per SIMD) per 256 x 256 output tile,
 // K consumed in steps of 64.  Each wavefront owns a 128 (N) x 128 (M) sub-tile = 8 x 8
 // blocks of the 16x16x32 bf16 MFMA; its 256 float32 accumulators live in the accumulation
@@ -38,6 +41,8 @@
 // only at row tails, section 3.1) are not in it, so they are neither computed nor counted
 // when the tiles are split across the XCDs.
 #include "device.h"
+#include "gemm_epilogue.h"
+#include "gemm_tiles.h"
 #include "kernels.h"
 
 namespace {
@@ -213,8 +218,8 @@ __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float x = c[i][e], y = c[i + 4][e];
-                        lo[e] = static_cast<bf16>(x * cv[e] - y * sv[e]);
-                        hi[e] = static_cast<bf16>(y * cv[e] + x * sv[e]);
+                        lo[e] = static_cast<bf16>(rope_lo(x, y, cv[e], sv[e]));
+                        hi[e] = static_cast<bf16>(rope_hi(x, y, cv[e], sv[e]));
                     }
                     stage_put<16>(stg, lr, 2 * i + (g >> 1), g & 1, lo);
                     stage_put<16>(stg, lr, 8 + 2 * i + (g >> 1), g & 1, hi);
@@ -522,35 +527,103 @@ namespace {
 
 constexpr size_t kLds = LDS_BYTES;
 
+int cu_count() {   // a multiple of 8, so that every XCD runs the same number of workgroups
+    static const int n = [] {
+        int dev = 0, v = 0;
+        (void)hipGetDevice(&dev);
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8) v = 8;
+        return v / 8 * 8;
+    }();
+    return n;
+}
+
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Output tiles of an XCD that takes the most of them, for tiles_m M-tiles of this kernel: each
+// XCD's block of M-tiles, or an equal share of the whole list where that saves a round of
+// workgroups.
+struct XcdSplit {
+    int balanced, tiles;
+};
+XcdSplit xcd_split(int tiles_m, int tiles_n, int wg_per_xcd) {
+    const int blocked = ceil_div(tiles_m, 8) * tiles_n, even = ceil_div(tiles_m * tiles_n, 8);
+    const int balanced = ceil_div(even, wg_per_xcd) < ceil_div(blocked, wg_per_xcd) ? 1 : 0;
+    return XcdSplit{balanced, balanced ? even : blocked};
+}
+
+// The first n_mt 256-row tiles on the 256 x 256 kernel.
 template <int EPI>
-void launch(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, int M, int N, int K,
-            const int32_t* mtile_m0, int n_mtiles, const QkvOut& qo, hipStream_t s) {
+void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
     static bool attr = [] {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         return true;
     }();
     (void)attr;
-    const int tiles_m = mtile_m0 ? n_mtiles : (M + BM - 1) / BM, tiles_n = N / BN;
-    if (tiles_m <= 0) return;
-    // one workgroup per CU (each needs the whole 160 KB LDS), a multiple of 8 so
-    // that every XCD runs the same number; never more workgroups than tiles
-    static const int n_cu = [] {
-        int dev = 0, n = 0;
-        (void)hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 8;
-        return n / 8 * 8;
-    }();
-    // per-XCD tile count of the M-block split and of the balanced one; the balanced split is
-    // taken only when it saves a whole round of workgroups
-    const int wg_per_xcd = n_cu / 8;
-    const int blocked = ((tiles_m + 7) / 8) * tiles_n, even = (tiles_m * tiles_n + 7) / 8;
-    const auto rounds = [&](int t) { return (t + wg_per_xcd - 1) / wg_per_xcd; };
-    const int balanced = rounds(even) < rounds(blocked) ? 1 : 0;
-    const int per_xcd = balanced ? even : blocked;
-    const dim3 grid(8 * min(wg_per_xcd, per_xcd));
-    gemm_bf16_kernel<EPI><<<grid, NT, kLds, s>>>(static_cast<const bf16*>(A), lda, static_cast<const bf16*>(B),
-                                                ldb, C, ldc, M, K, mtile_m0, tiles_m, tiles_n, balanced, qo);
+    // one workgroup per CU (each needs the whole 160 KB LDS); never more workgroups than tiles
+    const int tiles_n = g.N / BN, wg_per_xcd = cu_count() / 8;
+    const XcdSplit x = xcd_split(n_mt, tiles_n, wg_per_xcd);
+    const int M = g.mtile_m0 ? g.M : min(g.M, n_mt * BM);
+    gemm_bf16_kernel<EPI><<<8 * min(wg_per_xcd, x.tiles), NT, kLds, s>>>(
+        static_cast<const bf16*>(g.A), g.lda, static_cast<const bf16*>(g.B), g.ldb, g.C, g.ldc, M, g.K, g.mtile_m0, n_mt,
+        tiles_n, x.balanced, g.qkv);
+}
+
+// Which kernel takes which rows: the first `big` 256-row tiles on the 256 x 256 kernel, the rest
+// on tile size `tile` of gemm_tiles.
+//
+// The estimate: a kernel's time is the tiles of its busiest CU, each K / 64 steps of a measured
+// length (kBigStep, kTileStep; they hold within 10% over K 2048 .. 14336 and from one tile per CU
+// to twenty), and about 4 us for a launch.  The 256 x 256 tile has the best rate (1.34 us a step,
+// 1600 TFLOP/s on all CUs) but few rows make few tiles: at 344 rows N = 2048, K = 5504 gives it 16
+// tiles, 109 us, and 64 x 64 gives 192, 25 us.  One more M-tile than fills whole rounds costs a
+// round: the rows past the whole rounds then go to smaller tiles (2926 rows, N = 6144, K = 4096:
+// 288 tiles, two rounds, 191 us; 240 on one round and 366 rows as 128 x 128 tiles, 142 us).  A
+// split must promise 5%: past about 20 rounds the CUs no longer run in rounds, and a predicted
+// 2% (27,721 rows, N = 12288) measured as nothing.
+constexpr float kBigStep = 1.34f, kLaunch = 4.0f;
+
+struct GemmSplit {
+    int big, tile;
+};
+GemmSplit gemm_split(int n_mt, int M, int N, int K, bool list) {
+    const int tiles_n = N / BN, wg = cu_count() / 8;
+    const float steps = static_cast<float>(K / BK);
+    auto big_time = [&](int n) {
+        return n ? kLaunch + steps * kBigStep * ceil_div(xcd_split(n, tiles_n, wg).tiles, wg) : 0.f;
+    };
+    GemmSplit best{n_mt, 0};
+    float best_time = big_time(n_mt);
+    // rows left for the small tiles after `big` M-tiles: the last listed tile may be a short one
+    auto consider = [&](int big) {
+        const int rows = list ? (n_mt - big) * BM : M - big * BM;
+        const int last = list && n_mt == ceil_div(M, BM) ? n_mt * BM - M : 0;   // rows the last tile lacks
+        for (int t = 0; t < kGemmTiles; ++t) {
+            const int tiles = ceil_div(rows - last, kTileRows[t]) * (N / kTileCols[t]);
+            const float time = big_time(big) + kLaunch + steps * kTileStep[t] * ceil_div(ceil_div(tiles, 8), wg);
+            if (time < best_time * (big ? 0.95f : 1.f)) {
+                best_time = time;
+                best = GemmSplit{big, t};
+            }
+        }
+    };
+    // whole rounds of the large tile, one fewer, and none (first: a split competes with the rest)
+    consider(0);
+    const int rounds = n_mt * tiles_n / (8 * wg);
+    for (int r = rounds; r > 0 && r >= rounds - 1; --r) {
+        const int big = r * 8 * wg / tiles_n;
+        if (big > 0 && big < n_mt) consider(big);
+    }
+    return best;
+}
+
+template <int EPI>
+void gemm(const GemmArgs& g, int n_mtiles, hipStream_t s) {
+    const int n_mt = g.mtile_m0 ? n_mtiles : ceil_div(g.M, BM);
+    if (n_mt <= 0) return;
+    const GemmSplit sp = gemm_split(n_mt, g.M, g.N, g.K, g.mtile_m0 != nullptr);
+    if (sp.big > 0) launch<EPI>(g, sp.big, s);
+    if (sp.big < n_mt) gemm_tiles(EPI, sp.tile, g, sp.big, n_mt - sp.big, cu_count(), s);
 }
 
 }  // namespace
@@ -558,18 +631,18 @@ void launch(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int
 void gemm_bf16(int epi, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, int M,
                int N, int K, const int32_t* mtile_m0, int n_mtiles, hipStream_t s) {
     if (M <= 0) return;
-    const QkvOut none{};
+    const GemmArgs g{A, lda, B, ldb, C, ldc, M, N, K, mtile_m0, QkvOut{}};
     switch (epi) {
-        case kStore: launch<kStore>(A, lda, B, ldb, C, ldc, M, N, K, mtile_m0, n_mtiles, none, s); break;
-        case kResidual: launch<kResidual>(A, lda, B, ldb, C, ldc, M, N, K, mtile_m0, n_mtiles, none, s); break;
-        default: launch<kSwiGLU>(A, lda, B, ldb, C, ldc, M, N, K, mtile_m0, n_mtiles, none, s); break;
+        case kStore: gemm<kStore>(g, n_mtiles, s); break;
+        case kResidual: gemm<kResidual>(g, n_mtiles, s); break;
+        default: gemm<kSwiGLU>(g, n_mtiles, s); break;
     }
 }
 
 void qkv_rope_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int K, const int32_t* mtile_m0,
                    int n_mtiles, const QkvOut& out, hipStream_t s) {
     if (M <= 0) return;
-    launch<kQkvRope>(A, lda, B, ldb, nullptr, 0, M, (out.H + 2 * out.Hkv) * 128, K, mtile_m0, n_mtiles, out, s);
+    gemm<kQkvRope>(GemmArgs{A, lda, B, ldb, nullptr, 0, M, (out.H + 2 * out.Hkv) * 128, K, mtile_m0, out}, n_mtiles, s);
 }
 
 }  // namespace ppk

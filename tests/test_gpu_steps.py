@@ -103,6 +103,80 @@ def test_gemm_bf16_plan_row_tiles(epi):
         assert np.array_equal(got[~covered], base[~covered].astype(np.float64))
 
 
+# (M, N, K): every tile size of the projection GEMMs and the split of a batch between two of
+# them, with one row, tile edges + 1, fewer K-steps than the load ring holds (K = 64, 192) and an
+# odd number of them
+TILE_CASES = [(1, 256, 64), (33, 2048, 192), (65, 2048, 5504), (150, 6144, 2048), (344, 2048, 5504), (129, 512, 4160),
+              (344, 11008, 2048), (513, 4096, 14336), (700, 22016, 1024), (2926, 6144, 256), (1309, 11008, 128)]
+
+
+@pytest.mark.parametrize("M,N,K", TILE_CASES)
+@pytest.mark.parametrize("epi", [pp.PP_EPI_STORE, pp.PP_EPI_RESIDUAL, pp.PP_EPI_SWIGLU])
+def test_gemm_bf16_tiles(M, N, K, epi):
+    """Each call against float64, and bit for bit against the same rows inside a batch large
+    enough for the 256 x 256 tiles: a row's result does not depend on the tile that computed it."""
+    rng = np.random.default_rng([M, N, K, 3])
+    big = 4096 * 256 // N * 256 // 16 + 3 * 256 + M       # more than a round of large tiles
+    A, B = rand_bf16(rng, (big, K)), rand_bf16(rng, (N, K), 0.02)
+    a, b = bf16_dev(A), bf16_dev(B)
+    cols = N // 2 if epi == pp.PP_EPI_SWIGLU else N
+    dt = torch.float32 if epi == pp.PP_EPI_RESIDUAL else torch.bfloat16
+    c0 = torch.from_numpy(rng.standard_normal((big, cols)).astype(np.float32)).cuda().to(dt)
+    small, large = c0[:M + 1].clone(), c0.clone()
+    pp.pp_gemm(pp.PP_BF16, epi, a, K, b, K, small, cols, M, N, K)
+    pp.pp_gemm(pp.PP_BF16, epi, a, K, b, K, large, cols, big, N, K)
+    torch.cuda.synchronize()
+    assert torch.equal(small[:M], large[:M])
+    assert torch.equal(small[M], c0[M])                    # the row past M is not written
+    rows = np.unique(np.concatenate([rng.integers(0, M, min(M, 64)), [0, M - 1]]))
+    ref = A[rows].astype(np.float64) @ B.astype(np.float64).T
+    got = host64(small)[rows]
+    # a float32 accumulator is rounded once per 32-wide MFMA step (K / 32 times, at most 2^-23 of
+    # the partial sum each, truncation included); partial sums of these normal products stay below
+    # 6 sigma, sigma = |B's standard deviation| sqrt(K)
+    acc = (K / 32 + 1) * 2.0 ** -23 * 6 * 0.02 * np.sqrt(K)
+    if epi == pp.PP_EPI_RESIDUAL:
+        ref += host64(c0)[rows]
+        assert np.all(np.abs(got - ref) <= acc + 2.0 ** -23 * np.abs(ref))
+    elif epi == pp.PP_EPI_STORE:
+        assert within_ulps(got, ref, 1.0, acc) <= 1.0
+    else:
+        # |d(silu(g) u)| <= 1.1 |u| dg + |silu(g)| du, both factors below 6 sigma + 1
+        g = ref.reshape(len(rows), N // 32, 2, 16)         # 16 gate rows, then the matching 16 up rows
+        want = (D.silu(g[:, :, 0]) * g[:, :, 1]).reshape(len(rows), cols)
+        assert within_ulps(got, want, 1.0, 2.1 * acc * (6 * 0.02 * np.sqrt(K) + 1)) <= 1.0
+
+
+@pytest.mark.parametrize("lengths,H,Hkv,d", [([1], 2, 0, 256), ([40, 7], 16, 16, 2048), ([172, 145], 16, 16, 2048),
+                                             ([301, 300, 77], 32, 8, 4096), ([418] * 7, 32, 8, 4096)])
+def test_qkv_projection_tiles(lengths, H, Hkv, d):
+    """The fused QKV projection on each tile size: bit for bit what the same prompts get inside a
+    batch of large tiles."""
+    Hkv = Hkv or 2
+    rng = np.random.default_rng([sum(lengths), H, Hkv])
+    W = bf16_dev(rand_bf16(rng, ((H + 2 * Hkv) * 128, d), 0.02))
+    more = lengths + [max(lengths)] * -(-9000 // max(lengths))
+    x = rand_bf16(rng, (sum(more), d))
+
+    def run(ls):
+        plan = pp.pp_pack(ls, max(ls))
+        slots = torch.from_numpy(plan.slot_kv.astype(np.int64)).cuda()
+        xn = bf16_dev(x)[slots.clamp_min(0)] * (slots >= 0)[:, None].to(torch.bfloat16)
+        q = torch.zeros((plan.n_slots, H * 128), dtype=torch.bfloat16, device="cuda")
+        kc = torch.zeros((plan.total_len, Hkv * 128), dtype=torch.bfloat16, device="cuda")
+        vc = torch.zeros_like(kc)
+        table = torch.empty(plan.max_len * 128, dtype=torch.float32, device="cuda")
+        pp.pp_qkv_projection(_cfg(H, Hkv, d=d), pp.DevicePlan(plan), xn, W, table, q, kc, vc)
+        by_token = torch.zeros((plan.total_len, H * 128), dtype=torch.bfloat16, device="cuda")
+        by_token[slots[slots >= 0]] = q[slots >= 0]
+        torch.cuda.synchronize()
+        return by_token, kc, vc
+
+    n = sum(lengths)
+    for a, b in zip(run(lengths), run(more)):
+        assert torch.equal(a, b[:n])
+
+
 def test_gemm_f32():
     rng = np.random.default_rng(7)
     M, N, K = 77, 1376, 688
