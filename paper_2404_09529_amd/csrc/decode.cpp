@@ -13,9 +13,10 @@
 //              the residual adds of O and down happen in the norm that follows each
 //   final rmsnorm (float32) -> LM head and greedy choice (the first-token kernels, one
 //   row per prompt).
-// The projections: for bf16 steps of up to 64 prompts, weight-streaming GEMMs for one row
+// The projections: for bf16 steps of up to 16 prompts, weight-streaming GEMMs for one row
 // per prompt (QKV and gate/up with their epilogues in the kernel; O and down as split-K
-// partial sums that the next norm adds); otherwise the prefill's GEMM kernels with M = k.
+// partial sums that the next norm adds); up to 256 prompts the prefill's GEMM tiles, O and down
+// split likewise; otherwise the prefill's GEMM kernels with M = k.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,16 +49,8 @@ void projections(const pp_config* c, Proj (&p)[4]) {
     p[3] = {d, c->ffn_dim};                                       // down
 }
 
-// bf16 steps of up to 64 prompts take the skinny GEMM for every projection when the fused
-// residual norm takes the width (d <= 8192).
-bool use_skinny(const pp_config* c, int k) {
-    if (c->dtype != PP_BF16 || !ppk::residual_rmsnorm_ok(c->d_model)) return false;
-    Proj p[4];
-    projections(c, p);
-    for (const Proj& q : p)
-        if (!ppk::skinny_ok(k, q.N, q.K)) return false;
-    return true;
-}
+// bf16 widths whose O and down projections may leave partial sums to the residual norm.
+bool split_width(const pp_config* c) { return c->dtype == PP_BF16 && ppk::residual_rmsnorm_ok(c->d_model); }
 
 int chunks(int n) { return (n + ppk::kDecodeChunk - 1) / ppk::kDecodeChunk; }
 
@@ -85,16 +78,44 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.ints = take((4 * k + 1) * sizeof(int32_t));
     L.ft = take(ppk::first_token_workspace(c->dtype, g->k, c->vocab, c->d_model));
     size_t gpart = 0;
-    if (use_skinny(c, g->k)) {
+    if (split_width(c) && g->k <= 64) {
         Proj p[4];
         projections(c, p);
-        // O and down leave split-K partial sums
+        // O and down leave split-K partial sums (the tiles of 17 .. 64 prompts take as many
+        // splits as this holds)
         gpart = std::max(size_t(ppk::skinny_split(p[1].N, p[1].K).splits) * k * p[1].N * 4,
                          size_t(ppk::decode_gemm_splits(g->k, p[3].N, p[3].K)) * k * p[3].N * 4);
     }
     L.gpart = take(gpart);
     L.total = off;
     return L;
+}
+
+// How a step's projections run:
+//   kStream  up to 16 prompts at the widths they take: the weight-streaming kernels of k_decode.hip
+//   kTiles   up to 256: the prefill's GEMM tiles, O and down in up to `splits` K splits whose
+//            partial sums go to the workspace at `part`
+//   kWhole   the prefill's GEMMs as they are
+// The first two leave O's and down's partial sums to the norm that follows.  From 17 prompts on the
+// weights are no longer nearly all that a projection reads: the streaming kernels' wavefronts each
+// fetch every prompt's row, and O's workgroups each merge every prompt's attention chunks.  At 48
+// prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O, gate/up, down)
+// against 19 / 5 + 14 / 52 / 38 for the tiles (O with
+// its chunk merge as a kernel of its own).
+enum Mode { kStream, kTiles, kWhole };
+struct Plan {
+    Mode mode;
+    size_t part;
+    int splits;
+};
+Plan plan_of(const pp_config* c, const pp_gen_dlayout* g, const Layout& L) {
+    if (!split_width(c) || g->k > 256) return Plan{kWhole, 0, 0};
+    if (ppk::decode_stream_ok(g->k, c->d_model, c->n_heads * c->head_dim, c->ffn_dim)) return Plan{kStream, L.gpart, 0};
+    // past 64 prompts the partial sums take the place of the attention's chunk results, merged by
+    // then (two splits of d columns at least where H D >= d)
+    const size_t at = g->k <= 64 ? L.gpart : L.part, bytes = g->k <= 64 ? L.total - L.gpart : L.table - L.part;
+    const int splits = static_cast<int>(std::min<size_t>(bytes / (size_t(g->k) * c->d_model * 4), 16));
+    return splits > 0 ? Plan{kTiles, at, splits} : Plan{kWhole, 0, 0};
 }
 
 pp_status validate_layout(const pp_config* c, const pp_gen_dlayout* g) {
@@ -168,14 +189,15 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                                                                (g->ctx_rows + ppk::kDecodeChunk - 1) / ppk::kDecodeChunk + k));
     const ppk::DecodeLayout Ly{k, chunks(g->max_len), chunks(g->n_new), n_ctx_items, g->ctx_off, g->ctx_span,
                                g->ctx_valid, g->pos0, g->gen_off};
-    const bool skinny = use_skinny(cfg, k);
-    float* gpart = reinterpret_cast<float*>(ws + L.gpart);
+    const Plan plan = plan_of(cfg, g, L);
+    const bool split = plan.mode != kWhole;
+    float* gpart = reinterpret_cast<float*>(ws + plan.part);
 
     // the split-K residual projections (O, down) leave their partial sums in gpart; the next
     // norm adds them to x (pending = their split count) before normalising
     int pending = 0;
     auto norm = [&](const float* gain, void* out, int out_dtype) {
-        if (skinny)
+        if (split)
             ppk::residual_rmsnorm(out_dtype, x, gpart, pending, k, d, gain, out, eps, s);
         else
             ppk::rmsnorm(out_dtype, x, gain, out, k, d, eps, s);
@@ -189,7 +211,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
         void* gk = static_cast<char*>(gen_k) + l * gen_layer;
         void* gv = static_cast<char*>(gen_v) + l * gen_layer;
         norm(w->attn_norm[l], xn, dt);
-        if (skinny) {
+        if (plan.mode == kStream) {
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
             ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,
                              ppk::DecodeEpi{nullptr, 0, qo}, s);
@@ -201,7 +223,12 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
             ppk::qkv_rope_bf16(xn, d, w->wqkv[l], d, k, d, nullptr, 0, qo, s);
             ppk::decode_attention(dt, q, hd, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, attn, hd, s);
-            ppk::gemm_bf16(ppk::kResidual, attn, hd, w->wo[l], hd, x, d, k, d, hd, nullptr, 0, s);
+            if (split) {
+                ppk::gemm_partial_bf16(attn, hd, w->wo[l], hd, gpart, k, d, hd, plan.splits, s);
+                pending = ppk::gemm_partial_splits(k, d, hd, plan.splits);
+            } else {
+                ppk::gemm_bf16(ppk::kResidual, attn, hd, w->wo[l], hd, x, d, k, d, hd, nullptr, 0, s);
+            }
         } else {
             float* qkv32 = static_cast<float*>(q);
             ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->wqkv[l]), d,
@@ -213,7 +240,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                           hd, x, d, k, d, hd, s);
         }
         norm(w->mlp_norm[l], xn, dt);
-        if (skinny) {
+        if (plan.mode == kStream) {
             const ppk::QkvOut none{};
             ppk::decode_gemm(ppk::kSwiGLU, xn, d, k, w->w_gateup[l], d, 2 * F, d, gpart,
                              ppk::DecodeEpi{act, F, none}, s);
@@ -222,7 +249,12 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
             pending = ppk::decode_gemm_splits(k, d, F);
         } else if (bf) {
             ppk::gemm_bf16(ppk::kSwiGLU, xn, d, w->w_gateup[l], d, act, F, k, 2 * F, d, nullptr, 0, s);
-            ppk::gemm_bf16(ppk::kResidual, act, F, w->w_down[l], F, x, d, k, d, F, nullptr, 0, s);
+            if (split) {
+                ppk::gemm_partial_bf16(act, F, w->w_down[l], F, gpart, k, d, F, plan.splits, s);
+                pending = ppk::gemm_partial_splits(k, d, F, plan.splits);
+            } else {
+                ppk::gemm_bf16(ppk::kResidual, act, F, w->w_down[l], F, x, d, k, d, F, nullptr, 0, s);
+            }
         } else {
             ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->w_gateup[l]), d,
                           gu, 2 * F, k, 2 * F, d, s);

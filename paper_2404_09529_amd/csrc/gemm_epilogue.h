@@ -29,7 +29,19 @@ __device__ __forceinline__ void epilogue_direct(f32x4 (&acc)[NB][MB], void* __re
             c[i] = acc[i][j];
         }
     };
-    if constexpr (EPI == ppk::kResidual) {
+    if constexpr (EPI == ppk::kPartial) {
+        float* C = static_cast<float*>(Cv) + nb0 + 4 * g;
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            const int m = mb + 16 * j + lr;
+            f32x4 a[NB];
+            take(j, a);
+            if (m < M) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(C + int64_t(m) * ldc + 16 * i) = a[i];
+            }
+        }
+    } else if constexpr (EPI == ppk::kResidual) {
         float* C = static_cast<float*>(Cv) + nb0 + 4 * g;
 #pragma unroll
         for (int j = 0; j < MB; ++j) {

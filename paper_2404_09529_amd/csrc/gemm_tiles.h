@@ -28,6 +28,7 @@ constexpr float kTileStep[kGemmTiles] = {0.18f, 0.23f, 0.38f, 0.55f, 0.84f};
 
 // Entries mt_first .. mt_first + n_mt - 1 of the row-tile list (without one: of the 256-row tiles
 // of M) on tile size `tile`.  n_cu: a multiple of 8.
-void gemm_tiles(int epi, int tile, const GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s);
+// kPartial: K in `splits` pieces of whole steps, C = part[splits][M][ldc] float32.
+void gemm_tiles(int epi, int tile, const GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits = 1);
 
 }  // namespace ppk

@@ -15,26 +15,23 @@
 //                        from HBM once per step; it writes the chunk's (max, sum, output).
 // decode_combine_kernel  merges a prompt's chunk results in a fixed order (on the paths that
 //                        do not merge them in the O projection's staging, below).
-// The projections of a decode step have one row per prompt (k <= 64): C[k, N] = A[k, K]
-// W[N, K]^T is bound by streaming W from HBM.
-// rowpair_gemm_kernel    QKV and gate/up: one workgroup per 32 weight rows whose epilogue
-//                        belongs together (rotate-half pairs; gate and up rows of the same
-//                        features), K split four ways across its wavefronts and added
-//                        through LDS; RoPE with the query store and the key/value append,
-//                        or SwiGLU, in the same kernel.
-// rowpair_seg_kernel     the same for up to 16 prompts at K = 2048 or 4096, the weights
-//                        loaded as whole 1 KB row segments straight into an LDS ring.
+// The projections of a step of up to 16 prompts (more take the prefill's GEMM tiles): C[k, N] =
+// A[k, K] W[N, K]^T is bound by streaming W from HBM.
+// rowpair_seg_kernel     QKV and gate/up at K = 2048 or 4096: one workgroup per 32 weight
+//                        rows whose epilogue belongs together (rotate-half pairs; gate and up
+//                        rows of the same features), the weights loaded as whole 1 KB row
+//                        segments straight into an LDS ring, K split four ways across the
+//                        wavefronts and added through LDS; RoPE with the query store and the
+//                        key/value append, or SwiGLU, in the same kernel.
 // qkv_seg16_kernel       QKV in that style with 16 rows per workgroup (8 dims and their
 //                        rotate-half partners) when the 32-row groups outnumber the CUs.
-// splitk_seg_kernel      down (N = d) for up to 16 prompts in that style: 32 rows x a K
-//                        split per workgroup, float32 partial sums per split.
-// skinny_gemm_kernel     O, and down for more prompts (N = d, too few rows for one
-//                        workgroup per 32): about 512 pieces of 64 rows x a K split of up to
-//                        6 tiles of 128; each workgroup stages its slice of A (k rows, LDS
-//                        sized to k) once and each wavefront streams 16 weight rows into the
-//                        16x16x32 bf16 MFMA, all its K steps requested up front; float32
-//                        partial sums per split.  For O the staged slice is the attention
-//                        output, merged there from the chunk results.
+// splitk_seg_kernel      down (N = d) in that style: 32 rows x a K split per workgroup, float32
+//                        partial sums per split.
+// o_proj_kernel          O (N = d): about 512 pieces of 64 rows x a K split of up to 6 tiles of
+//                        128; each workgroup forms its slice of the attention output once, in
+//                        LDS, merged from the chunk results, and each wavefront streams 16
+//                        weight rows into the 16x16x32 bf16 MFMA, all its K steps requested up
+//                        front; float32 partial sums per split.
 // residual_rmsnorm_kernel  adds those partial sums, in split order, to the residual stream
 //                        inside the RMSNorm that follows each projection.
 // (A single-kernel split-K with the sum done by the last workgroup of a row group was
@@ -358,17 +355,17 @@ constexpr int SG_ROWS = 64;     // W rows per workgroup, 16 per wavefront
 constexpr int SG_TILE = 128;    // K columns per staged A tile
 constexpr int SG_MAX_TILES = 6; // A tiles per K split (4: 1.2% slower at the 7B shape; 8: 0.6%)
 
-// part[s][m][n] = sum over the NT K tiles of split s of A[m, :] . W[n, :], m < k <= 16 NMB.
+// part[s][m][n] = sum over the NT K tiles of split s of A[m, :] . W[n, :], m < k <= 16, A the
+// attention output.
 // Lane l of wavefront w reads 8 consecutive K values of W row n_w + l % 16 at offset
 // 8 (l / 16) of each 32-wide step, every step of its split requested before the first MFMA,
-// and holds, per prompt block mb, the sums of prompt 16 mb + l % 16 for rows
-// n_w + 4 (l / 16) + 0..3.  The slice of A (k_pad rows x NT tiles) is staged once in LDS.
-template <int NT, int NMB, bool COMB>
-__global__ __launch_bounds__(256) void skinny_gemm_kernel(const bf16* __restrict__ A, int64_t lda, int k,
-                                                          const bf16* __restrict__ W, int64_t ldw, int N, int K,
-                                                          float* __restrict__ part, ppk::AttnChunks ac) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];   // NT tiles of 16 NMB rows x 256 bytes
-    constexpr int KP = 16 * NMB, TILE_B = KP * 256;
+// and holds the sums of prompt l % 16 for rows n_w + 4 (l / 16) + 0..3.  The slice of A (16 rows
+// x NT tiles) is formed once in LDS.
+template <int NT>
+__global__ __launch_bounds__(256) void o_proj_kernel(int k, const bf16* __restrict__ W, int64_t ldw, int N, int K,
+                                                     float* __restrict__ part, ppk::AttnChunks ac) {
+    constexpr int KP = 16, TILE_B = KP * 256;
+    __shared__ __attribute__((aligned(16))) char lds[NT * TILE_B];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int lr = lane & 15, q4 = lane >> 4;
     const int g = blockIdx.x, s = blockIdx.y;   // row group, K split
@@ -380,23 +377,17 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const bf16* __restrict
 #pragma unroll
     for (int j = 0; j < 4 * NT; ++j)
         if (j < 4 * nt) ring[j] = *reinterpret_cast<const bf16x8*>(wrow + 32 * j);
-    // stage A[0 .. KP) x tiles t0 .. t0 + nt (rows past k read as row k - 1, or zero when
-    // merged from chunks; their sums are never stored).
-    // COMB: A is the attention output, formed here from the decode attention's chunk results
-    // (128 columns = one head per tile): the chunks of prompt r and head t0 + t merged in
-    // the fixed order of decode_combine_kernel, divided by the sum, rounded to bf16.
+    // A[0 .. KP) x tiles t0 .. t0 + nt, formed from the decode attention's chunk results (128
+    // columns = one head per tile): the chunks of prompt r and head t0 + t merged in the fixed
+    // order of decode_combine_kernel, divided by the sum, rounded to bf16; rows past k are zero
+    // (their sums are never stored).
     for (int idx = threadIdx.x; idx < KP * nt * 16; idx += 256) {
         const int r = idx / (nt * 16), q = idx % (nt * 16), t = q / 16, ch = q % 16;
-        const int m = min(r, k - 1);
         bf16x8 v{};
-        if constexpr (COMB) {
-            if (r >= k) {   // padding rows of the tile: their sums are never stored
-                *reinterpret_cast<bf16x8*>(lds + t * TILE_B + r * 256 + 16 * (ch ^ gsw(r & 7))) = v;
-                continue;
-            }
+        if (r < k) {
             constexpr int PS = 128 + 4;
-            const float* base = ac.part + (int64_t(m) * ac.H + t0 + t) * ac.n_chunks * PS;
-            const int nc = (ac.ctx_span[m] + CH - 1) / CH, ng = (ac.step + 1 + CH - 1) / CH;
+            const float* base = ac.part + (int64_t(r) * ac.H + t0 + t) * ac.n_chunks * PS;
+            const int nc = (ac.ctx_span[r] + CH - 1) / CH, ng = (ac.step + 1 + CH - 1) / CH;
             float mm = -INFINITY, ll = 0.f, o[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = 0.f;
@@ -427,8 +418,6 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const bf16* __restrict
             const float inv = ll > 0.f ? 1.f / ll : 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = static_cast<bf16>(o[e] * inv);
-        } else {
-            v = *reinterpret_cast<const bf16x8*>(A + int64_t(m) * lda + int64_t(t0 + t) * SG_TILE + ch * 8);
         }
         *reinterpret_cast<bf16x8*>(lds + t * TILE_B + r * 256 + 16 * (ch ^ gsw(r & 7))) = v;
     }
@@ -437,24 +426,17 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const bf16* __restrict
 #pragma unroll
     for (int j = 0; j < 4 * NT; ++j) asm volatile("" : "+v"(ring[j]));
     __syncthreads();
-    f32x4 acc[NMB] = {};
+    f32x4 acc = {};
     const int fsw = gsw(lr & 7);
 #pragma unroll
     for (int j = 0; j < 4 * NT; ++j) {
         if (j < 4 * nt) {
-#pragma unroll
-            for (int mb = 0; mb < NMB; ++mb) {
-                const bf16x8 h = *reinterpret_cast<const bf16x8*>(lds + (j / 4) * TILE_B + (16 * mb + lr) * 256 +
-                                                                  16 * ((4 * (j % 4) + q4) ^ fsw));
-                acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ring[j], h, acc[mb], 0, 0, 0);
-            }
+            const bf16x8 h =
+                *reinterpret_cast<const bf16x8*>(lds + (j / 4) * TILE_B + lr * 256 + 16 * ((4 * (j % 4) + q4) ^ fsw));
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ring[j], h, acc, 0, 0, 0);
         }
     }
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) {
-        const int m = 16 * mb + lr;
-        if (m < k) *reinterpret_cast<f32x4*>(part + (int64_t(s) * k + m) * N + n_w + 4 * q4) = acc[mb];
-    }
+    if (lr < k) *reinterpret_cast<f32x4*>(part + (int64_t(s) * k + lr) * N + n_w + 4 * q4) = acc;
 }
 
 // RoPE (query and key heads) and the stores of one prompt m's dims i .. i + 3 (a) and their
@@ -504,92 +486,22 @@ __device__ __forceinline__ void rowpair_epilogue(int g, int m, int c, const f32x
     }
 }
 
-// Decode projections whose epilogue needs two blocks of 16 weight rows together, SwiGLU (the
-// 16 gate rows and the 16 up rows of 16 features) and QKV (16 rotate-half pairs c, c + 64 of
-// a head): one workgroup per such 32 rows, its 4 wavefronts each taking a quarter of K, the
-// quarters added in wavefront order through LDS and the epilogue applied in the same kernel
-// (no partial sums leave the workgroup).  Weight and activation fragments are read straight
-// from global memory into a ring of RP_RING steps.  Lane l: weight row r_nb + l % 16 and
-// prompt 16 mb + l % 16, K offset 8 (l / 16) of each 32-wide step; it ends with block nb's
-// rows r_nb + 4 (l / 16) + 0..3 for prompt 16 mb + l % 16.
-constexpr int RP_RING = 2;   // 2: 52 VGPRs; 4, 6 and 8 (132 VGPRs) measured 1-3% slower at the 7B shape
-
-template <int EPI, int NMB>
-__global__ __launch_bounds__(256) void rowpair_gemm_kernel(const bf16* __restrict__ A, int64_t lda, int k,
-                                                           const bf16* __restrict__ W, int64_t ldw, int K,
-                                                           ppk::DecodeEpi ep) {
-    __shared__ f32x4 red[4][2][NMB][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int lr = lane & 15, q4 = lane >> 4;
-    const int g = blockIdx.x;
-    int r0[2];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-        r0[nb] = EPI == ppk::kSwiGLU ? 32 * g + 16 * nb : (g >> 2) * 128 + 64 * nb + 16 * (g & 3);
-    const int kq = K / 4, k0 = w * kq, steps = kq / 32;
-    const bf16* wp[2];
-    const bf16* ap[NMB];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) wp[nb] = W + int64_t(r0[nb] + lr) * ldw + k0 + 8 * q4;
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) ap[mb] = A + int64_t(min(16 * mb + lr, k - 1)) * lda + k0 + 8 * q4;
-    bf16x8 rw[RP_RING][2], ra[RP_RING][NMB];
-    auto issue = [&](int u, int j) {
-        const int jj = 32 * min(j, steps - 1);
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) rw[u][nb] = *reinterpret_cast<const bf16x8*>(wp[nb] + jj);
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) ra[u][mb] = *reinterpret_cast<const bf16x8*>(ap[mb] + jj);
-    };
-#pragma unroll
-    for (int u = 0; u < RP_RING; ++u) issue(u, u);
-    f32x4 acc[2][NMB] = {};
-    for (int j0 = 0; j0 < steps; j0 += RP_RING) {
-#pragma unroll
-        for (int u = 0; u < RP_RING; ++u) {
-            if (j0 + u < steps) {
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int mb = 0; mb < NMB; ++mb)
-                        acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rw[u][nb], ra[u][mb], acc[nb][mb], 0, 0, 0);
-            }
-            if (j0 + u + RP_RING < steps) issue(u, j0 + u + RP_RING);
-        }
-    }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) red[w][nb][mb][lane] = acc[nb][mb];
-    __syncthreads();
-    for (int it = threadIdx.x; it < NMB * 64; it += 256) {
-        const int mb = it / 64, l = it % 64;
-        const int m = 16 * mb + (l & 15), c = 4 * (l >> 4);   // prompt, first of 4 rows of each block
-        if (m >= k) continue;
-        f32x4 a = red[0][0][mb][l], b = red[0][1][mb][l];
-#pragma unroll
-        for (int w2 = 1; w2 < 4; ++w2) {
-            a += red[w2][0][mb][l];
-            b += red[w2][1][mb][l];
-        }
-        rowpair_epilogue<EPI>(g, m, c, a, b, ep);
-    }
-}
-
 // Buffer descriptor word 3 for raw (unstructured) 32-bit-offset loads on gfx9-family parts.
 constexpr int kRsrcWord3 = 0x00020000;
 // s_waitcnt immediate: vmcnt(n) and lgkmcnt(0), expcnt not waited for (gfx9 encoding).
 constexpr int wait_vm_lgkm0(int n) { return ((n >> 4) << 14) | (n & 15) | 0x0070; }
 typedef __attribute__((address_space(3))) void lds_void;
 
-// The rowpair projections for up to 16 prompts with K = 512 NSEG: the same 32 rows per workgroup
-// and epilogue, the weights streamed as whole 1 KB row segments.  Chunk (s, nb) = the 16 rows of
+// Decode projections whose epilogue needs two blocks of 16 weight rows together, SwiGLU (the
+// 16 gate rows and the 16 up rows of 16 features) and QKV (16 rotate-half pairs c, c + 64 of
+// a head), for up to 16 prompts with K = 512 NSEG: one workgroup per such 32 rows, the weights
+// streamed as whole 1 KB row segments.  Chunk (s, nb) = the 16 rows of
 // block nb x K columns 512 s .. + 511; each wavefront loads 4 of its rows (one 1 KB load each)
 // straight into an LDS ring of NW chunks, which from HBM runs markedly faster than the 64-byte
 // pieces of 16 rows that register loads in the MFMA layout request.  Wavefront w takes columns
 // 128 w .. + 127 of every chunk (4 K-steps); its quarter of the prompts' rows (4 fragments per
 // segment) goes into registers one segment ahead of its use.  The quarters' sums are added
-// through LDS in wavefront order, as in rowpair_gemm_kernel.
+// through LDS in wavefront order.
 constexpr int RS_COLS = 512;                    // K columns of a chunk
 constexpr int RS_CHUNK_B = 16 * RS_COLS * 2;    // 16 KB
 
@@ -804,22 +716,25 @@ void launch_rowpair_seg(int N, hipStream_t s, const bf16* A, int64_t lda, int k,
     rowpair_seg_kernel<EPI, NSEG, NW><<<N / 32, 256, lds, s>>>(A, lda, k, W, ldw, ep);
 }
 
-// Whether rowpair_seg_kernel takes the shape: up to 16 prompts, K = 2048 or 4096.  The ring
-// depth follows the grid: three workgroups of 48 KB per CU when there are more than 512 of
-// them, else two of 64 KB.
-template <int EPI>
-bool launch_rowpair_seg_for(int N, int K, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W,
-                            int64_t ldw, const ppk::DecodeEpi& ep) {
-    if (k > 16 || (K != 2048 && K != 4096)) return false;
-    const bool wide = N / 32 > 512;
-    if (K == 4096) {
-        if (wide) launch_rowpair_seg<EPI, 8, 3>(N, s, A, lda, k, W, ldw, ep);
-        else launch_rowpair_seg<EPI, 8, 4>(N, s, A, lda, k, W, ldw, ep);
-    } else {
-        if (wide) launch_rowpair_seg<EPI, 4, 3>(N, s, A, lda, k, W, ldw, ep);
-        else launch_rowpair_seg<EPI, 4, 4>(N, s, A, lda, k, W, ldw, ep);
-    }
-    return true;
+// rowpair_seg_kernel's ring depth follows the grid: three workgroups of 48 KB per CU when there
+// are more than 512 of them, else two of 64 KB.
+template <int EPI, int NSEG>
+void launch_rowpair(int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
+                    const ppk::DecodeEpi& ep) {
+    if (N / 32 > 512) launch_rowpair_seg<EPI, NSEG, 3>(N, s, A, lda, k, W, ldw, ep);
+    else launch_rowpair_seg<EPI, NSEG, 4>(N, s, A, lda, k, W, ldw, ep);
+}
+
+// QKV and gate/up at K = 512 NSEG.
+template <int NSEG>
+void launch_paired(int epi, int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
+                   const ppk::DecodeEpi& ep) {
+    // QKV: 16-row workgroups when the 32-row groups outnumber the CUs (7B: 384 groups become 768
+    // workgroups, 21.4 -> 20.5 us); with fewer groups (Mistral-7B and 1.3B: 192) the 32-row
+    // kernel is faster (16 rows: 2.6% and 3.7% slower steps)
+    if (epi == ppk::kSwiGLU) launch_rowpair<ppk::kSwiGLU, NSEG>(N, s, A, lda, k, W, ldw, ep);
+    else if (N / 32 > 256) launch_qkv_seg16<NSEG, 3>(N, s, A, lda, k, W, ldw, ep.qkv);
+    else launch_rowpair<ppk::kQkvRope, NSEG>(N, s, A, lda, k, W, ldw, ep);
 }
 
 // Split-K projection for up to 16 prompts (the down projection, whose N = d leaves too few
@@ -963,18 +878,6 @@ SegSplit seg_split(int k, int N, int K) {
     return SegSplit{s, splits};
 }
 
-template <int EPI>
-void launch_rowpair(int nmb, int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
-                    int K, const ppk::DecodeEpi& ep) {
-    const dim3 grid(N / 32);
-    switch (nmb) {
-        case 1: rowpair_gemm_kernel<EPI, 1><<<grid, 256, 0, s>>>(A, lda, k, W, ldw, K, ep); break;
-        case 2: rowpair_gemm_kernel<EPI, 2><<<grid, 256, 0, s>>>(A, lda, k, W, ldw, K, ep); break;
-        case 3: rowpair_gemm_kernel<EPI, 3><<<grid, 256, 0, s>>>(A, lda, k, W, ldw, K, ep); break;
-        default: rowpair_gemm_kernel<EPI, 4><<<grid, 256, 0, s>>>(A, lda, k, W, ldw, K, ep); break;
-    }
-}
-
 // Residual add of a split-K projection fused with the RMSNorm that follows it, one workgroup
 // of d / (4 E) threads per prompt row, 4 E consecutive elements per thread (E = 1 up to
 // d = 4096, 2 up to 8192): x[m] += sum over splits of part[.][m], added in split order, stored
@@ -1036,44 +939,6 @@ __global__ __launch_bounds__(1024) void residual_rmsnorm_kernel(float* __restric
         } else {
             *reinterpret_cast<f32x4*>(out + int64_t(m) * d + c + 4 * e) = v[e] * r * gg[e];
         }
-    }
-}
-
-template <int NT, bool COMB>
-void launch_skinny_nt(int nmb, dim3 grid, size_t lds, hipStream_t s, const bf16* A, int64_t lda, int k,
-                      const bf16* W, int64_t ldw, int N, int K, float* part, const ppk::AttnChunks& ac) {
-    // the staged slice of A takes NT x 16 nmb rows x 256 bytes: up to 96 KB, past the 64 KB
-    // a launch gets without asking
-    static const bool attr = [] {
-        auto allow = [](const void* f, int nmb_) {
-            (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, NT * 16 * nmb_ * 256);
-        };
-        allow(reinterpret_cast<const void*>(&skinny_gemm_kernel<NT, 1, COMB>), 1);
-        allow(reinterpret_cast<const void*>(&skinny_gemm_kernel<NT, 2, COMB>), 2);
-        allow(reinterpret_cast<const void*>(&skinny_gemm_kernel<NT, 3, COMB>), 3);
-        allow(reinterpret_cast<const void*>(&skinny_gemm_kernel<NT, 4, COMB>), 4);
-        return true;
-    }();
-    (void)attr;
-    switch (nmb) {
-        case 1: skinny_gemm_kernel<NT, 1, COMB><<<grid, 256, lds, s>>>(A, lda, k, W, ldw, N, K, part, ac); break;
-        case 2: skinny_gemm_kernel<NT, 2, COMB><<<grid, 256, lds, s>>>(A, lda, k, W, ldw, N, K, part, ac); break;
-        case 3: skinny_gemm_kernel<NT, 3, COMB><<<grid, 256, lds, s>>>(A, lda, k, W, ldw, N, K, part, ac); break;
-        default: skinny_gemm_kernel<NT, 4, COMB><<<grid, 256, lds, s>>>(A, lda, k, W, ldw, N, K, part, ac); break;
-    }
-}
-
-template <bool COMB>
-void launch_skinny(int nt, int nmb, dim3 grid, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W,
-                   int64_t ldw, int N, int K, float* part, const ppk::AttnChunks& ac) {
-    const size_t lds = size_t(nt) * 16 * nmb * 256;
-    switch (nt) {
-        case 1: launch_skinny_nt<1, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
-        case 2: launch_skinny_nt<2, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
-        case 3: launch_skinny_nt<3, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
-        case 4: launch_skinny_nt<4, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
-        case 5: launch_skinny_nt<5, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
-        default: launch_skinny_nt<6, COMB>(nmb, grid, lds, s, A, lda, k, W, ldw, N, K, part, ac); break;
     }
 }
 
@@ -1156,7 +1021,9 @@ int decode_gemm_splits(int k, int N, int K) {
     return ss.s ? ss.splits : skinny_split(N, K).splits;
 }
 
-bool skinny_ok(int k, int N, int K) { return k >= 1 && k <= 64 && N % SG_ROWS == 0 && K % SG_TILE == 0; }
+bool decode_stream_ok(int k, int d, int hd, int F) {
+    return k >= 1 && k <= 16 && (d == 2048 || d == 4096) && hd % SG_TILE == 0 && F % 128 == 0;
+}
 
 void residual_rmsnorm(int dtype_out, float* x, const float* part, int S, int k, int d, const float* g, void* out,
                       float eps, hipStream_t s) {
@@ -1181,46 +1048,35 @@ bool residual_rmsnorm_ok(int d) { return d > 0 && (d <= 4096 ? d % 256 == 0 : d 
 
 void decode_gemm(int epi, const void* A, int64_t lda, int k, const void* W, int64_t ldw, int N, int K, float* part,
                  const DecodeEpi& ep, hipStream_t s) {
-    const int nmb = (k + 15) / 16;
     const bf16* a = static_cast<const bf16*>(A);
     const bf16* w = static_cast<const bf16*>(W);
-    if (epi == kSwiGLU) {
-        if (!launch_rowpair_seg_for<kSwiGLU>(N, K, s, a, lda, k, w, ldw, ep))
-            launch_rowpair<kSwiGLU>(nmb, N, s, a, lda, k, w, ldw, K, ep);
+    if (epi != kResidual) {
+        if (K == 4096) launch_paired<8>(epi, N, s, a, lda, k, w, ldw, ep);
+        else launch_paired<4>(epi, N, s, a, lda, k, w, ldw, ep);   // 2048
         return;
     }
-    if (epi == kQkvRope) {
-        // 16-row workgroups when the 32-row groups outnumber the CUs (7B: 384 groups become 768
-        // workgroups, 21.4 -> 20.5 us); with fewer groups (Mistral-7B and 1.3B: 192) the 32-row
-        // kernel is faster (16 rows: 2.6% and 3.7% slower steps)
-        if (k <= 16 && (K == 2048 || K == 4096) && N / 32 > 256) {
-            if (K == 4096) launch_qkv_seg16<8, 3>(N, s, a, lda, k, w, ldw, ep.qkv);
-            else launch_qkv_seg16<4, 3>(N, s, a, lda, k, w, ldw, ep.qkv);
-            return;
-        }
-        if (!launch_rowpair_seg_for<kQkvRope>(N, K, s, a, lda, k, w, ldw, ep))
-            launch_rowpair<kQkvRope>(nmb, N, s, a, lda, k, w, ldw, K, ep);
-        return;
-    }
-    // kResidual: split-K partial sums, added to the residual stream by residual_rmsnorm
+    // split-K partial sums, added to the residual stream by residual_rmsnorm
     const SegSplit ss = seg_split(k, N, K);
     switch (ss.s) {
         case 4: return launch_splitk_seg<4, 3>(N, ss.splits, s, a, lda, k, w, ldw, K, part);
         case 2: return launch_splitk_seg<2, 3>(N, ss.splits, s, a, lda, k, w, ldw, K, part);
-        case 1: return launch_splitk_seg<1, 3>(N, ss.splits, s, a, lda, k, w, ldw, K, part);
-        default: break;   // s = 0: the skinny kernel
+        default: return launch_splitk_seg<1, 3>(N, ss.splits, s, a, lda, k, w, ldw, K, part);
     }
-    const SkinnySplit sp = skinny_split(N, K);
-    const AttnChunks none{};
-    launch_skinny<false>(sp.tiles_per_split, nmb, dim3(N / SG_ROWS, sp.splits), s, a, lda, k, w, ldw, N, K, part,
-                         none);
 }
 
 void decode_gemm_o(int k, const AttnChunks& ac, const void* W, int64_t ldw, int N, int K, float* part,
                    hipStream_t s) {
     const SkinnySplit sp = skinny_split(N, K);
-    launch_skinny<true>(sp.tiles_per_split, (k + 15) / 16, dim3(N / SG_ROWS, sp.splits), s, nullptr, 0, k,
-                        static_cast<const bf16*>(W), ldw, N, K, part, ac);
+    const dim3 grid(N / SG_ROWS, sp.splits);
+    const bf16* w = static_cast<const bf16*>(W);
+    switch (sp.tiles_per_split) {
+        case 1: o_proj_kernel<1><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+        case 2: o_proj_kernel<2><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+        case 3: o_proj_kernel<3><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+        case 4: o_proj_kernel<4><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+        case 5: o_proj_kernel<5><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+        default: o_proj_kernel<6><<<grid, 256, 0, s>>>(k, w, ldw, N, K, part, ac); break;
+    }
 }
 
 }  // namespace ppk

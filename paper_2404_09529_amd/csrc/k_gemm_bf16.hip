@@ -617,6 +617,31 @@ GemmSplit gemm_split(int n_mt, int M, int N, int K, bool list) {
     return best;
 }
 
+// kPartial's tile and K splits for M rows of a decode step: the same estimate, with enough splits
+// to give the CUs something to do (N = d leaves 64 tiles of 64 x 64 at d 4096) against 8 bytes per
+// partial sum, written here and read by the norm, at about 4 TB/s.
+struct PartialSplit {
+    int tile, splits;
+};
+PartialSplit partial_split(int M, int N, int K, int max_splits) {
+    const int steps = K / BK, wg = cu_count() / 8;
+    PartialSplit best{0, 1};
+    float best_time = 1e30f;
+    for (int t = 0; t < kGemmTiles; ++t) {
+        if (N % kTileCols[t]) continue;
+        for (int s = 1; s <= max_splits && s <= 16 && s <= steps; ++s) {
+            const int tiles = ceil_div(M, kTileRows[t]) * (N / kTileCols[t]) * s;
+            const float time = ceil_div(steps, s) * kTileStep[t] * ceil_div(ceil_div(tiles, 8), wg) +
+                               float(s) * M * N * 8e-6f / 4.f;
+            if (time < best_time) {
+                best_time = time;
+                best = PartialSplit{t, s};
+            }
+        }
+    }
+    return best;
+}
+
 template <int EPI>
 void gemm(const GemmArgs& g, int n_mtiles, hipStream_t s) {
     const int n_mt = g.mtile_m0 ? n_mtiles : ceil_div(g.M, BM);
@@ -643,6 +668,15 @@ void qkv_rope_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, int M
                    int n_mtiles, const QkvOut& out, hipStream_t s) {
     if (M <= 0) return;
     gemm<kQkvRope>(GemmArgs{A, lda, B, ldb, nullptr, 0, M, (out.H + 2 * out.Hkv) * 128, K, mtile_m0, out}, n_mtiles, s);
+}
+
+int gemm_partial_splits(int M, int N, int K, int max_splits) { return partial_split(M, N, K, max_splits).splits; }
+
+void gemm_partial_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, float* part, int M, int N, int K,
+                       int max_splits, hipStream_t s) {
+    const PartialSplit sp = partial_split(M, N, K, max_splits);
+    gemm_tiles(kPartial, sp.tile, GemmArgs{A, lda, B, ldb, part, N, M, N, K, nullptr, QkvOut{}}, 0, ceil_div(M, BM),
+               cu_count(), s, sp.splits);
 }
 
 }  // namespace ppk

@@ -115,7 +115,9 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
         m0 = (mtile_m0 ? mtile_m0[entry] : entry * kListRows) + mt % SUB * BM;
         n0 = EPI == ppk::kQkvRope && BN == 64 ? nt / 2 * 128 + nt % 2 * 32 : nt * BN;
     };
-    const int nk = K / BK;
+    // this workgroup's K-steps (all of them but for kPartial's splits, blockIdx.y of gridDim.y)
+    const int k_first = K / BK * blockIdx.y / gridDim.y, nk = K / BK * (blockIdx.y + 1) / gridDim.y - k_first;
+    if constexpr (EPI == ppk::kPartial) Cv = static_cast<float*>(Cv) + int64_t(blockIdx.y) * M * ldc;
 
     // ---- direct global -> LDS loads: each fills 1 KB = 8 rows x 128 bytes of a slot, lane l
     // landing at physical chunk l % 8 of row l / 8 and fetching the logical chunk that the
@@ -160,7 +162,8 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
         char* dst = smem + l_slot * G::SLOT_B + (is_a ? (G::A_LD * wave + t) * 1024
                                                       : BM * ROW_B + (G::B_LD * wave + t - G::A_LD) * 1024);
         const int voff = is_a ? voff_a[is_a ? t : 0] : voff_b[is_a ? 0 : t - G::A_LD];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_b, (lds_void*)dst, 16, voff, l_kt * ROW_B, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_b, (lds_void*)dst, 16, voff, (k_first + l_kt) * ROW_B,
+                                                 0, 0);
     };
     auto advance_cursor = [&]() {
         l_slot = l_slot == NS - 1 ? 0 : l_slot + 1;
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
 
 // TILE: index into kTileRows / kTileCols; NS ring slots, WGS workgroups per CU.
 template <int EPI, int TILE, int NS, int WGS>
-void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s) {
+void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits) {
     constexpr int BM = ppk::kTileRows[TILE], BN = ppk::kTileCols[TILE];
     using G = Geom<BM, BN, NS>;
     static_assert(WGS * G::LDS <= 160 * 1024, "LDS of a CU's workgroups");
@@ -262,19 +265,19 @@ void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_
     (void)attr;
     const int64_t tiles = int64_t(n_mt) * (kListRows / BM) * (g.N / BN);   // at least the kernel's count
     const int64_t grid = 8 * std::min<int64_t>((tiles + 7) / 8, WGS * (n_cu / 8));
-    gemm_tiles_kernel<EPI, BM, BN, NS, WGS><<<static_cast<unsigned>(grid), NT, G::LDS, s>>>(
+    gemm_tiles_kernel<EPI, BM, BN, NS, WGS><<<dim3(static_cast<unsigned>(grid), splits), NT, G::LDS, s>>>(
         static_cast<const bf16*>(g.A), g.lda, static_cast<const bf16*>(g.B), g.ldb, g.C, g.ldc, g.M, g.N, g.K, g.mtile_m0,
         mt_first, n_mt, g.qkv);
 }
 
 template <int EPI>
-void launch_tile(int tile, const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s) {
+void launch_tile(int tile, const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits) {
     switch (tile) {
-        case 0: return launch<EPI, 0, 6, 2>(g, mt_first, n_mt, n_cu, s);
-        case 1: return launch<EPI, 1, 5, 2>(g, mt_first, n_mt, n_cu, s);
-        case 2: return launch<EPI, 2, 3, 2>(g, mt_first, n_mt, n_cu, s);
-        case 3: return launch<EPI, 3, 5, 1>(g, mt_first, n_mt, n_cu, s);
-        default: return launch<EPI, 4, 3, 1>(g, mt_first, n_mt, n_cu, s);
+        case 0: return launch<EPI, 0, 6, 2>(g, mt_first, n_mt, n_cu, s, splits);
+        case 1: return launch<EPI, 1, 5, 2>(g, mt_first, n_mt, n_cu, s, splits);
+        case 2: return launch<EPI, 2, 3, 2>(g, mt_first, n_mt, n_cu, s, splits);
+        case 3: return launch<EPI, 3, 5, 1>(g, mt_first, n_mt, n_cu, s, splits);
+        default: return launch<EPI, 4, 3, 1>(g, mt_first, n_mt, n_cu, s, splits);
     }
 }
 
@@ -282,12 +285,13 @@ void launch_tile(int tile, const ppk::GemmArgs& g, int mt_first, int n_mt, int n
 
 namespace ppk {
 
-void gemm_tiles(int epi, int tile, const GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s) {
+void gemm_tiles(int epi, int tile, const GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits) {
     switch (epi) {
-        case kStore: return launch_tile<kStore>(tile, g, mt_first, n_mt, n_cu, s);
-        case kResidual: return launch_tile<kResidual>(tile, g, mt_first, n_mt, n_cu, s);
-        case kSwiGLU: return launch_tile<kSwiGLU>(tile, g, mt_first, n_mt, n_cu, s);
-        default: return launch_tile<kQkvRope>(tile, g, mt_first, n_mt, n_cu, s);
+        case kStore: return launch_tile<kStore>(tile, g, mt_first, n_mt, n_cu, s, splits);
+        case kResidual: return launch_tile<kResidual>(tile, g, mt_first, n_mt, n_cu, s, splits);
+        case kSwiGLU: return launch_tile<kSwiGLU>(tile, g, mt_first, n_mt, n_cu, s, splits);
+        case kPartial: return launch_tile<kPartial>(tile, g, mt_first, n_mt, n_cu, s, splits);
+        default: return launch_tile<kQkvRope>(tile, g, mt_first, n_mt, n_cu, s, splits);
     }
 }
 

@@ -34,7 +34,7 @@ void kv_scatter(int dtype, const void* qkv, int64_t ld, int k_col, int kvw, void
 void swiglu_f32(const float* gu, float* act, int T, int F, hipStream_t s);
 
 // Epilogues of the projection GEMMs C = A B^T (A [M, K] activations, B [N, K] weights).
-enum Epilogue { kStore = 0, kResidual = 1, kSwiGLU = 2, kQkvRope = 3 };
+enum Epilogue { kStore = 0, kResidual = 1, kSwiGLU = 2, kQkvRope = 3, kPartial = 4 };
 
 // Destinations of the kQkvRope epilogue.  B is the stacked [Wq; Wk; Wv] with head dim 128;
 // q [M, ldq] receives the rotated queries, kc / vc [*, ldkv] the rotated keys and the values
@@ -64,6 +64,13 @@ void gemm_bf16(int epi, const void* A, int64_t lda, const void* B, int64_t ldb, 
 // N = (H + 2 Hkv) * 128; row tiles as gemm_bf16.
 void qkv_rope_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int K,
                    const int32_t* mtile_m0, int n_mtiles, const QkvOut& out, hipStream_t s);
+
+// Split-K form of gemm_bf16 for the residual projections of a decode step: part[s][M][N] float32,
+// the sums of K split s (S of them, summed by residual_rmsnorm).  gemm_partial_splits: the number
+// of splits it takes, at most max_splits (>= 1).  N % 64 == 0, K % 64 == 0.
+int gemm_partial_splits(int M, int N, int K, int max_splits);
+void gemm_partial_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, float* part, int M, int N, int K,
+                       int max_splits, hipStream_t s);
 
 // float32 FMA GEMM (kStore / kResidual).  Requires K % 16 == 0.
 void gemm_f32(int epi, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
@@ -141,15 +148,16 @@ struct DecodeEpi {
     QkvOut qkv;
 };
 
-// K split of the skinny GEMM: `splits` pieces of `tiles_per_split` 128-column tiles.
+// K split of decode_gemm_o: `splits` pieces of `tiles_per_split` 128-column tiles.
 struct SkinnySplit {
     int tiles_per_split, splits;
 };
 SkinnySplit skinny_split(int N, int K);
-// Shapes the skinny GEMM takes: 1 <= k <= 64 rows, N % 64 == 0, K % 128 == 0.
-bool skinny_ok(int k, int N, int K);
+// Shapes decode_gemm and decode_gemm_o take (bf16, head dim 128): up to 16 prompts at widths d of
+// 2048 or 4096, the query width hd = H D and F multiples of 128.
+bool decode_stream_ok(int k, int d, int hd, int F);
 
-// The O projection of a decode step (bf16, head dim 128, k <= 64): its activations are the
+// The O projection of a decode step (bf16, head dim 128, k <= 16): its activations are the
 // attention output, merged from the attention's chunk results while they are staged; float32
 // split-K partial sums in part for residual_rmsnorm, as decode_gemm's kResidual.
 void decode_gemm_o(int k, const AttnChunks& ac, const void* W, int64_t ldw, int N, int K, float* part,
@@ -162,13 +170,14 @@ void residual_rmsnorm(int dtype_out, float* x, const float* part, int S, int k, 
 // Widths residual_rmsnorm takes: d % 256 == 0 up to 4096, d % 512 == 0 up to 8192.
 bool residual_rmsnorm_ok(int d);
 
-// bf16 C = A W^T for k <= 64 rows (A [k, lda], W [N, ldw]) with the epilogue `epi`:
-// kSwiGLU and kQkvRope in the GEMM kernel itself (N % 32 == 0); kResidual leaves float32
-// partial sums in part (decode_gemm_splits(k, N, K) * k * N floats) for residual_rmsnorm to
-// add.
+// bf16 C = A W^T for k <= 16 rows (A [k, lda], W [N, ldw]) with the epilogue `epi`:
+// kSwiGLU and kQkvRope in the GEMM kernel itself (N % 32 == 0; K 2048 or 4096); kResidual
+// leaves float32 partial sums in part (decode_gemm_splits(k, N, K) * k * N floats) for
+// residual_rmsnorm to add.
 void decode_gemm(int epi, const void* A, int64_t lda, int k, const void* W, int64_t ldw, int N, int K, float* part,
                  const DecodeEpi& ep, hipStream_t s);
-// The number of K splits decode_gemm's kResidual leaves for k rows of an N x K product.
+// The number of K splits decode_gemm's kResidual leaves for k <= 16 rows of an N x K product (for
+// more rows, what the workspace's room for partial sums is sized by).
 int decode_gemm_splits(int k, int N, int K);
 
 }  // namespace ppk

@@ -102,7 +102,11 @@ def test_fp32_generate_matches_oracle(lengths, n_new, n_layers):
 # a width past 4096 (the fused residual norm's 8-elements-per-thread form), 13B-like
 WIDE = {"d5120": dict(d_model=5120, n_heads=40, n_kv_heads=40, ffn_dim=13824),
         # F = 5248 = 10 x 512 + 128: the down projection's last 1 KB segment holds 128 columns
-        "f5248": dict(d_model=2048, n_heads=16, n_kv_heads=16, ffn_dim=5248)}
+        "f5248": dict(d_model=2048, n_heads=16, n_kv_heads=16, ffn_dim=5248),
+        # a width the weight-streaming kernels do not take: GEMM tiles at any prompt count
+        "d1024": dict(d_model=1024, n_heads=8, n_kv_heads=4, ffn_dim=2816),
+        # H D < d: the partial sums of more than 64 prompts have room for one K split only
+        "h2": dict(d_model=1024, n_heads=2, n_kv_heads=2, ffn_dim=1024)}
 
 
 def _bf16_case(model_name, lengths, n_layers, seed=0):
@@ -178,6 +182,17 @@ def test_bf16_decode_steps_teacher_forced(model_name, lengths, n_layers, n_new):
 
 
 # ----------------------------------------------------------------------------- layouts and entry points agree
+@pytest.mark.parametrize("model_name,lengths,n_layers,n_new", [
+    ("llama2-7b", [3] * 16 + [150], 1, 2),                            # 17 prompts: the first count on the tiles
+    ("d1024", [9, 130, 1], 2, 3),
+    ("d1024", [2, 5, 1] * 43, 1, 2),                                  # 129 prompts: partial sums over the chunks
+    ("h2", [2, 1] * 33, 1, 2),
+    ("d1024", [1, 2] * 128 + [1], 1, 2),                              # 257 prompts: the prefill's GEMMs as they are
+])
+def test_bf16_decode_steps_on_gemm_tiles(model_name, lengths, n_layers, n_new):
+    test_bf16_decode_steps_teacher_forced(model_name, lengths, n_layers, n_new)
+
+
 @pytest.mark.parametrize("model_name,lengths,n_layers,n_new", [
     ("llama-1.3b", [1, 300, 7, 129, 1, 64], 1, 5),
     ("mistral-7b", [700, 2, 33], 1, 5),
