@@ -7,7 +7,7 @@
 //
 //   decode_prep (positions, RoPE rows, append rows); embed of the k fed tokens
 //   per layer: rmsnorm -> QKV projection with RoPE and the append to the generation cache
-//              (bf16: the prefill's fused epilogue; float32: GEMM, RoPE, scatter) ->
+//              (the prefill's fused epilogue) ->
 //              split-key decode attention + combine -> O GEMM (+residual) -> rmsnorm ->
 //              gate/up GEMM with SwiGLU -> down GEMM (+residual); with the split-K GEMMs
 //              the residual adds of O and down happen in the norm that follows each
@@ -33,7 +33,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 size_t elem_size(int dtype) { return dtype == PP_BF16 ? 2 : 4; }
 
 struct Layout {
-    size_t x = 0, xn = 0, q = 0, attn = 0, act = 0, gu = 0, h = 0, part = 0, table = 0, ints = 0, ft = 0, gpart = 0,
+    size_t x = 0, xn = 0, q = 0, attn = 0, act = 0, h = 0, part = 0, table = 0, ints = 0, ft = 0, gpart = 0,
            total = 0;
 };
 
@@ -71,7 +71,6 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.q = take(c->dtype == PP_BF16 ? k * hd * 2 : k * qkv_w * 4);   // bf16: rotated queries only
     L.attn = take(k * hd * e);
     L.act = take(k * F * e);
-    L.gu = take(c->dtype == PP_F32 ? k * 2 * F * 4 : 0);
     L.h = take(k * d * 4);
     L.part = take(k * size_t(c->n_heads) * nch * (D + 4) * 4);
     L.table = take(k * (D / 2) * sizeof(float2));
@@ -174,7 +173,6 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
     void* q = ws + L.q;
     void* attn = ws + L.attn;
     void* act = ws + L.act;
-    float* gu = reinterpret_cast<float*>(ws + L.gu);
     float* h = reinterpret_cast<float*>(ws + L.h);
     float* part = reinterpret_cast<float*>(ws + L.part);
     float2* table = reinterpret_cast<float2*>(ws + L.table);
@@ -230,11 +228,8 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                 ppk::gemm_bf16(ppk::kResidual, attn, hd, w->wo[l], hd, x, d, k, d, hd, nullptr, 0, s);
             }
         } else {
-            float* qkv32 = static_cast<float*>(q);
-            ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->wqkv[l]), d,
-                          qkv32, qkv_w, k, qkv_w, d, s);
-            ppk::rope_apply(dt, q, qkv_w, table, slot_pos, slot_seg, k, H + Hkv, D, s);
-            ppk::kv_scatter(dt, q, qkv_w, hd, kvw, gk, gv, slot_kv, k, s);
+            const ppk::QkvOut qo{q, qkv_w, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
+            ppk::qkv_rope_f32(static_cast<const float*>(xn), d, static_cast<const float*>(w->wqkv[l]), d, k, d, D, qo, s);
             ppk::decode_attention(dt, q, qkv_w, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, attn, hd, s);
             ppk::gemm_f32(ppk::kResidual, static_cast<const float*>(attn), hd, static_cast<const float*>(w->wo[l]),
                           hd, x, d, k, d, hd, s);
@@ -256,9 +251,8 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                 ppk::gemm_bf16(ppk::kResidual, act, F, w->w_down[l], F, x, d, k, d, F, nullptr, 0, s);
             }
         } else {
-            ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->w_gateup[l]), d,
-                          gu, 2 * F, k, 2 * F, d, s);
-            ppk::swiglu_f32(gu, static_cast<float*>(act), k, F, s);
+            ppk::gemm_f32(ppk::kSwiGLU, static_cast<const float*>(xn), d, static_cast<const float*>(w->w_gateup[l]), d,
+                          static_cast<float*>(act), F, k, 2 * F, d, s);
             ppk::gemm_f32(ppk::kResidual, static_cast<const float*>(act), F, static_cast<const float*>(w->w_down[l]),
                           F, x, d, k, d, F, s);
         }

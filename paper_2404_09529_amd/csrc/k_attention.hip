@@ -33,8 +33,8 @@
 //     work item (one per query head) are spread so that each XCD serves whole KV heads: the
 //     tiles of a prompt that read the same keys and values run at the same time on the same
 //     XCD and share its L2.
-// float32 kernel: one wavefront per (query slot, head), a plain online-softmax loop over
-// the query's keys, used for float32 models.
+// float32 kernel: one wavefront per (query slot, head), an online softmax over tiles of 64 keys,
+// used for float32 models.
 #include "device.h"
 #include "kernels.h"
 #include "prepack.h"
@@ -331,6 +331,13 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_kernel(const bf16* __restrict
 }
 
 // ----------------------------------------------------------------------------- float32
+// One wavefront per (query slot, head), keys in tiles of 64: lane j holds key j's score (its own
+// dot product over the head, so no reduction across lanes per key), one maximum and one sum across
+// the lanes per tile, then lane d accumulates dims d (and d + 64) over the tile's keys, the
+// probabilities read lane by lane.  The serial chain is per tile, not per key: 384 slots x 4 heads
+// of 64 over at most 61 keys took 52 us with a reduction per key, 9 us now.  Keys past the
+// prompt (a padded span's tail) are zero: score 0, value 0.
+template <int D>
 __global__ __launch_bounds__(NT) void attn_f32_kernel(const float* __restrict__ q, int64_t ldq,
                                                       const float* __restrict__ kc, const float* __restrict__ vc,
                                                       int64_t ldkv, float* __restrict__ out, int64_t ldo,
@@ -338,9 +345,10 @@ __global__ __launch_bounds__(NT) void attn_f32_kernel(const float* __restrict__ 
                                                       const int32_t* __restrict__ seg_prompt,
                                                       const int32_t* __restrict__ seg_start,
                                                       const int32_t* __restrict__ prompt_kv_off, int T, int H,
-                                                      int Hkv, int D, float scale) {
+                                                      int Hkv, float scale) {
+    constexpr int E = D / 64;   // dims per lane
     const int lane = threadIdx.x & 63;
-    const int64_t wid = int64_t(blockIdx.x) * (NT / kWave) + (threadIdx.x >> 6);
+    const int64_t wid = int64_t(blockIdx.x) * (NT / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t slot = wid / H;
     if (slot >= T) return;
     const int h = static_cast<int>(wid - slot * H);
@@ -350,35 +358,61 @@ __global__ __launch_bounds__(NT) void attn_f32_kernel(const float* __restrict__ 
     const int prompt = seg_prompt[seg];
     const int64_t kv0 = prompt_kv_off[prompt];
     const int plen = prompt_kv_off[prompt + 1] - static_cast<int>(kv0);
-    const int g = h / (H / Hkv);
+    const int64_t col = int64_t(h / (H / Hkv)) * D;
     const float* qr = q + slot * ldq + int64_t(h) * D;
-    float qv[2], acc[2] = {0.f, 0.f};
+    const float* K = kc + kv0 * ldkv + col;
+    const float* V = vc + kv0 * ldkv + col + lane;
+    float m = -INFINITY, l = 0.f, acc[E];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) qv[c] = lane + 64 * c < D ? qr[lane + 64 * c] : 0.f;
-    float m = -INFINITY, l = 0.f;
-    for (int j = 0; j <= qi; ++j) {
-        // keys past the prompt (a padded span's tail) are zero: score 0, value 0
-        const bool real = j < plen;
-        const float* k = kc + (kv0 + j) * ldkv + int64_t(g) * D;
-        const float* v = vc + (kv0 + j) * ldkv + int64_t(g) * D;
-        float part = 0.f;
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+    for (int j0 = 0; j0 <= qi; j0 += 64) {
+        const int j = j0 + lane;
+        float s = -INFINITY;
+        if (j <= qi) {
+            float d4[4] = {0.f, 0.f, 0.f, 0.f};
+            if (j < plen) {
+                const float* k = K + int64_t(j) * ldkv;
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            if (real && lane + 64 * c < D) part += qv[c] * k[lane + 64 * c];
-        const float sc = wave_sum(part) * scale;
-        const float m_new = fmaxf(m, sc);
-        const float corr = expf(m - m_new);
-        const float p = expf(sc - m_new);
-        l = l * corr + p;
+                for (int c = 0; c < D; c += 4) {
+                    const f32x4 kk = *reinterpret_cast<const f32x4*>(k + c);
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            if (lane + 64 * c < D) acc[c] = acc[c] * corr + (real ? p * v[lane + 64 * c] : 0.f);
+                    for (int e = 0; e < 4; ++e) d4[e] = fmaf(qr[c + e], kk[e], d4[e]);
+                }
+            }
+            s = ((d4[0] + d4[1]) + (d4[2] + d4[3])) * scale;
+        }
+        const float m_new = fmaxf(m, wave_max(s));   // key j0 is allowed: a number, unless a score is NaN
+        const float corr = expf(m - m_new);          // 0 at the first tile (m = -inf)
+        const float p = expf(s - m_new);             // 0 past the query
+        l = l * corr + wave_sum(p);
         m = m_new;
-    }
-    float* o = out + slot * ldo + int64_t(h) * D;
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-        if (lane + 64 * c < D) o[lane + 64 * c] = acc[c] / l;
+        for (int e = 0; e < E; ++e) acc[e] *= corr;
+        const int n = min(min(64, qi + 1 - j0), plen - j0);   // keys past the prompt add nothing
+        const float* v = V + int64_t(j0) * ldkv;
+        int i = 0;
+        for (; i + 8 <= n; i += 8) {
+            float vv[8][E];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int e = 0; e < E; ++e) vv[u][e] = v[int64_t(i + u) * ldkv + 64 * e];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float pu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), i + u));
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fmaf(pu, vv[u][e], acc[e]);
+            }
+        }
+        for (; i < n; ++i) {
+            const float pu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), i));
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = fmaf(pu, v[int64_t(i) * ldkv + 64 * e], acc[e]);
+        }
+    }
+    float* o = out + slot * ldo + int64_t(h) * D + lane;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[64 * e] = acc[e] / l;
 }
 
 }  // namespace
@@ -409,8 +443,13 @@ void attention_f32(const float* q, int64_t ldq, const float* kc, const float* vc
     const int64_t waves = int64_t(T) * H;
     if (waves == 0) return;
     const unsigned blocks = static_cast<unsigned>((waves + NT / kWave - 1) / (NT / kWave));
-    attn_f32_kernel<<<blocks, NT, 0, s>>>(q, ldq, kc, vc, ldkv, out, ldo, slot_seg, seg_prompt, seg_start,
-                                          prompt_kv_off, T, H, Hkv, D, 1.0f / sqrtf(static_cast<float>(D)));
+    const float scale = 1.0f / sqrtf(static_cast<float>(D));
+    if (D == 64)
+        attn_f32_kernel<64><<<blocks, NT, 0, s>>>(q, ldq, kc, vc, ldkv, out, ldo, slot_seg, seg_prompt, seg_start,
+                                                  prompt_kv_off, T, H, Hkv, scale);
+    else
+        attn_f32_kernel<128><<<blocks, NT, 0, s>>>(q, ldq, kc, vc, ldkv, out, ldo, slot_seg, seg_prompt, seg_start,
+                                                   prompt_kv_off, T, H, Hkv, scale);
 }
 
 }  // namespace ppk

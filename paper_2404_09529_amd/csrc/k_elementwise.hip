@@ -208,16 +208,6 @@ __global__ __launch_bounds__(kBlock) void kv_scatter_kernel(const T* __restrict_
     store8(dst, v);
 }
 
-__global__ __launch_bounds__(kBlock) void swiglu_f32_kernel(const float* __restrict__ gu, float* __restrict__ act,
-                                                            int T_, int F) {
-    const int64_t idx = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (idx >= int64_t(T_) * F) return;
-    const int64_t t = idx / F;
-    const int f = static_cast<int>(idx % F);
-    const int64_t gi = t * 2 * F + 32 * (f / 16) + f % 16;
-    act[idx] = silu(gu[gi]) * gu[gi + 16];
-}
-
 unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
 
 }  // namespace
@@ -270,12 +260,6 @@ void kv_scatter(int dtype, const void* qkv, int64_t ld, int k_col, int kvw, void
     else
         kv_scatter_kernel<float><<<blocks_for(n), kBlock, 0, s>>>(static_cast<const float*>(qkv), ld, k_col, kvw,
                                                                   at<float>(kc), at<float>(vc), slot_kv, T);
-}
-
-void swiglu_f32(const float* gu, float* act, int T, int F, hipStream_t s) {
-    const int64_t n = int64_t(T) * F;
-    if (n == 0) return;
-    swiglu_f32_kernel<<<blocks_for(n), kBlock, 0, s>>>(gu, act, T, F);
 }
 
 }  // namespace ppk

@@ -1,62 +1,147 @@
-// float32 projection GEMM C = A B^T (A [M, K] activations, B [N, K] weights) for float32
-// models: 64 x 64 output tiles, K steps of 16 staged through LDS, 4 x 4 outputs per
-// thread on FMA units.  Used by the small float32 decoder; bf16 models use the MFMA GEMM.
+// float32 projection GEMM C = A B^T (A [M, K] activations, B [N, K] weights) for float32 models,
+// on the float32 matrix instructions (16x16x4: float32 products and sums).
+//
+// What bounds it at the sizes a float32 model has (d 256, a few hundred rows): latency.  So many
+// small workgroups, no staging and few dependent steps: a 256-thread workgroup takes a 32 x 32
+// tile, each of its 4 wavefronts a quarter of K (in steps of 16, the steps dealt round-robin), with
+// its operands loaded straight into the lanes that multiply them and kDepth steps in flight; the
+// four quarters are added through LDS in wavefront order.  An element's sum does not depend on M
+// or on the tile's place, so packed and padded batches agree bit for bit.
+// Measured (us; 64 x 64 tiles on the vector units with a barrier per 16 columns before -> now):
+// 384 rows, N 768, K 256: 24 -> 8; N 256, K 688: 67 -> 7; 4096 rows, N = K = 4096:
+// 2237 -> 1977.
+//
+// Epilogues: store; residual add; SwiGLU over gate/up rows interleaved in blocks of 16 (a tile's 32
+// weight rows are the gate and up rows of 16 features); QKV with RoPE at the restart positions and
+// the cache UNPACK (a tile's rows are 16 dims of a head and their rotate-half partners).
 #include "device.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int TB = 64, TK = 16, NT = 256;
+constexpr int TB = 32, TK = 16, NT = 256, kDepth = 4;
 
 template <int EPI>
 __global__ __launch_bounds__(NT) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
                                                       const float* __restrict__ B, int64_t ldb,
-                                                      float* __restrict__ C, int64_t ldc, int M, int N, int K) {
-    __shared__ float sa[TK][TB + 4];
-    __shared__ float sb[TK][TB + 4];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int64_t m0 = int64_t(blockIdx.y) * TB;
-    const int n0 = blockIdx.x * TB;
-    const int r = tid >> 2, kq = (tid & 3) * 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += TK) {
-        const f32x4 va = m0 + r < M ? *reinterpret_cast<const f32x4*>(A + (m0 + r) * lda + k0 + kq) : f32x4{};
-        const f32x4 vb = n0 + r < N ? *reinterpret_cast<const f32x4*>(B + int64_t(n0 + r) * ldb + k0 + kq)
-                                    : f32x4{};
+                                                      float* __restrict__ C, int64_t ldc, int M, int N, int K,
+                                                      int vec, ppk::QkvOut qo, int D) {
+    __shared__ f32x4 red[4][4][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, q4 = lane >> 4;
+    const int tiles_n = (N + TB - 1) / TB;
+    const int m0 = blockIdx.x / tiles_n * TB, t = blockIdx.x % tiles_n;
+    // first weight row of the tile's two blocks of 16
+    int n0 = t * TB, n1 = n0 + 16;
+    if constexpr (EPI == ppk::kQkvRope) {
+        const int per_head = D / TB;
+        n0 = t / per_head * D + t % per_head * 16;
+        n1 = n0 + D / 2;
+    }
+    // lane l supplies row l % 16 of each block at columns 4 (l / 16) .. + 3 of a step: 16 rows x
+    // 64 bytes a load; rows past the matrix read its last row (never stored)
+    const float* a[2];
+    const float* b[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sa[kq + e][r] = va[e];
-            sb[kq + e][r] = vb[e];
+    for (int i = 0; i < 2; ++i) {
+        a[i] = A + int64_t(min(m0 + 16 * i + lr, M - 1)) * lda + 4 * q4;
+        b[i] = B + int64_t(min((i ? n1 : n0) + lr, N - 1)) * ldb + 4 * q4;
+    }
+    const int steps = K / TK;
+    f32x4 ra[kDepth][2], rb[kDepth][2];
+    auto issue = [&](int u, int s) {   // step s of this wavefront's (clamped) into slot u
+        const int k = TK * min(wave + 4 * s, steps - 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            ra[u][i] = *reinterpret_cast<const f32x4*>(a[i] + k);
+            rb[u][i] = *reinterpret_cast<const f32x4*>(b[i] + k);
         }
-        __syncthreads();
+    };
+    const int n_mine = (steps - wave + 3) / 4;   // may be 0 where K < 64
 #pragma unroll
-        for (int kk = 0; kk < TK; ++kk) {
-            float av[4], bv[4];
+    for (int u = 0; u < kDepth; ++u) issue(u, u);
+    f32x4 acc[2][2] = {};   // [weight block][activation block]
+    for (int s0 = 0; s0 < n_mine; s0 += kDepth) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = sa[kk][ty + 16 * i];
+        for (int u = 0; u < kDepth; ++u) {
+            if (s0 + u < n_mine) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = sb[kk][tx + 16 * j];
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[u][i][e], ra[u][j][e], acc[i][j], 0, 0, 0);
+            }
+            if (s0 + u + kDepth < n_mine) issue(u, s0 + u + kDepth);
         }
-        __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + ty + 16 * i;
-        if (m >= M) continue;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx + 16 * j;
-            if (n >= N) continue;
-            if constexpr (EPI == ppk::kResidual)
-                C[m * ldc + n] += acc[i][j];
-            else
-                C[m * ldc + n] = acc[i][j];
+        for (int j = 0; j < 2; ++j) red[wave][2 * i + j][lane] = acc[i][j];
+    __syncthreads();
+    // wavefront w < 2 finishes activation block w: rows m0 + 16 w + l % 16, weight rows
+    // 4 (l / 16) + 0..3 of both blocks
+    if (wave >= 2) return;
+    f32x4 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        v[i] = red[0][2 * i + wave][lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v[i] += red[w][2 * i + wave][lane];
+    }
+    const int m = m0 + 16 * wave + lr, c = 4 * q4;
+    if (m >= M) return;
+    if constexpr (EPI == ppk::kSwiGLU) {
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = silu(v[0][e]) * v[1][e];
+        *reinterpret_cast<f32x4*>(C + m * ldc + t * 16 + c) = o;
+    } else if constexpr (EPI == ppk::kQkvRope) {
+        const int head = n0 / D, i0 = n0 % D + c;
+        const int kind = head < qo.H ? 0 : (head < qo.H + qo.Hkv ? 1 : 2);   // q, k, v
+        if (kind < 2) {
+            const float2* cs = qo.table + int64_t(qo.slot_pos[m]) * (D / 2) + i0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = v[0][e], y = v[1][e];
+                v[0][e] = rope_lo(x, y, cs[e].x, cs[e].y);
+                v[1][e] = rope_hi(x, y, cs[e].x, cs[e].y);
+            }
+        }
+        const int row = kind == 0 ? m : qo.slot_kv[m];
+        if (row < 0) return;   // a pad slot has no cache row
+        float* dst = kind == 0 ? static_cast<float*>(qo.q) + row * qo.ldq + head * D
+                               : static_cast<float*>(kind == 1 ? qo.kc : qo.vc) + row * qo.ldkv +
+                                     (head - qo.H - (kind == 2 ? qo.Hkv : 0)) * D;
+        *reinterpret_cast<f32x4*>(dst + i0) = v[0];
+        *reinterpret_cast<f32x4*>(dst + i0 + D / 2) = v[1];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = (i ? n1 : n0) + c;
+            float* p = C + m * ldc + n;
+            if (vec && n + 4 <= N) {   // vec: C's rows are 16-byte aligned
+                f32x4 o = v[i];
+                if constexpr (EPI == ppk::kResidual) o += *reinterpret_cast<f32x4*>(p);
+                *reinterpret_cast<f32x4*>(p) = o;
+            } else {
+                for (int e = 0; e < 4 && n + e < N; ++e) p[e] = EPI == ppk::kResidual ? p[e] + v[i][e] : v[i][e];
+            }
         }
     }
+}
+
+template <int EPI>
+void launch(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int M, int N, int K,
+            const ppk::QkvOut& qo, int D, hipStream_t s) {
+    if (M <= 0 || N <= 0) return;
+    const unsigned tiles = static_cast<unsigned>(int64_t((N + TB - 1) / TB) * ((M + TB - 1) / TB));
+    const int vec = ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
+    gemm_f32_kernel<EPI><<<tiles, NT, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K, vec, qo, D);
 }
 
 }  // namespace
@@ -65,12 +150,17 @@ namespace ppk {
 
 void gemm_f32(int epi, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int M,
               int N, int K, hipStream_t s) {
-    if (M <= 0 || N <= 0) return;
-    const dim3 grid((N + TB - 1) / TB, (M + TB - 1) / TB);
-    if (epi == kResidual)
-        gemm_f32_kernel<kResidual><<<grid, NT, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K);
-    else
-        gemm_f32_kernel<kStore><<<grid, NT, 0, s>>>(A, lda, B, ldb, C, ldc, M, N, K);
+    const QkvOut none{};
+    switch (epi) {
+        case kResidual: return launch<kResidual>(A, lda, B, ldb, C, ldc, M, N, K, none, 0, s);
+        case kSwiGLU: return launch<kSwiGLU>(A, lda, B, ldb, C, ldc, M, N, K, none, 0, s);
+        default: return launch<kStore>(A, lda, B, ldb, C, ldc, M, N, K, none, 0, s);
+    }
+}
+
+void qkv_rope_f32(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int K, int D, const QkvOut& out,
+                  hipStream_t s) {
+    launch<kQkvRope>(A, lda, B, ldb, nullptr, 0, M, (out.H + 2 * out.Hkv) * D, K, out, D, s);
 }
 
 }  // namespace ppk

@@ -30,16 +30,13 @@ void rope_apply(int dtype, void* qkv, int64_t ld, const float2* table, const int
 void kv_scatter(int dtype, const void* qkv, int64_t ld, int k_col, int kvw, void* kc, void* vc,
                 const int32_t* slot_kv, int T, hipStream_t s);
 
-// act[t][f] = SiLU(gu[t][g(f)]) * gu[t][g(f) + 16], g(f) = 32 (f / 16) + f % 16 (float32 path).
-void swiglu_f32(const float* gu, float* act, int T, int F, hipStream_t s);
-
 // Epilogues of the projection GEMMs C = A B^T (A [M, K] activations, B [N, K] weights).
 enum Epilogue { kStore = 0, kResidual = 1, kSwiGLU = 2, kQkvRope = 3, kPartial = 4 };
 
-// Destinations of the kQkvRope epilogue.  B is the stacked [Wq; Wk; Wv] with head dim 128;
+// Destinations of the kQkvRope epilogue.  B is the stacked [Wq; Wk; Wv] (bf16: head dim 128);
 // q [M, ldq] receives the rotated queries, kc / vc [*, ldkv] the rotated keys and the values
 // of every slot with slot_kv >= 0 at row slot_kv.  Rotation angles come from table
-// (float2 [positions][64]) at slot_pos (0 for slots outside every span).
+// (float2 [positions][D / 2]) at slot_pos (0 for slots outside every span).
 struct QkvOut {
     void* q;
     int64_t ldq;
@@ -72,9 +69,14 @@ int gemm_partial_splits(int M, int N, int K, int max_splits);
 void gemm_partial_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, float* part, int M, int N, int K,
                        int max_splits, hipStream_t s);
 
-// float32 FMA GEMM (kStore / kResidual).  Requires K % 16 == 0.
+// float32 GEMM (kStore / kResidual; kSwiGLU as gemm_bf16, C float32 [M, ldc], N % 32 == 0).
+// Requires K % 16 == 0.
 void gemm_f32(int epi, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
               int M, int N, int K, hipStream_t s);
+
+// The float32 QKV projection with RoPE and the cache UNPACK; head dim D 64 or 128.
+void qkv_rope_f32(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int K, int D, const QkvOut& out,
+                  hipStream_t s);
 
 // Attention over segments (independent mask): for every query slot of every work-list
 // tile, softmax(q k^T / sqrt(D)) v over the keys of its own segment at or before it.

@@ -5,8 +5,7 @@
 //
 //   rope_table; embed (TENSORIZE through the slot map)
 //   per layer: rmsnorm -> QKV projection with RoPE at restart positions and the KV UNPACK
-//              fused into its epilogue (bf16; float32 runs GEMM, RoPE and scatter as three
-//              launches) -> attention under the independent mask, keys and values read
+//              fused into its epilogue -> attention under the independent mask, keys and values read
 //              from the caches -> O GEMM (+residual) -> rmsnorm -> gate/up GEMM with
 //              SwiGLU -> down GEMM (+residual)
 //   final rmsnorm fused with the hidden-state UNPACK.
@@ -24,7 +23,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t x = 0, xn = 0, qkv = 0, attn = 0, act = 0, gu = 0, table = 0, total = 0;
+    size_t x = 0, xn = 0, qkv = 0, attn = 0, act = 0, table = 0, total = 0;
 };
 
 size_t elem_size(int dtype) { return dtype == PP_BF16 ? 2 : 4; }
@@ -75,7 +74,6 @@ Layout layout_of(const pp_config* c, const pp_dplan* p) {
     L.qkv = take(c->dtype == PP_BF16 ? T * hd * 2 : T * qkv_w * 4);   // bf16: queries only
     L.attn = take(T * hd * e);
     L.act = take(T * F * e);
-    L.gu = take(c->dtype == PP_F32 ? T * 2 * F * 4 : 0);
     L.table = take(size_t(p->max_len) * (c->head_dim / 2) * sizeof(float2));
     L.total = off;
     return L;
@@ -175,7 +173,6 @@ extern "C" pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const
     void* qkv = ws + L.qkv;
     void* attn = ws + L.attn;
     void* act = ws + L.act;
-    float* gu = reinterpret_cast<float*>(ws + L.gu);
     float2* table = reinterpret_cast<float2*>(ws + L.table);
     const size_t cache_layer_bytes = size_t(plan->total_len) * kvw * e;
 
@@ -192,11 +189,9 @@ extern "C" pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const
                                 plan->prompt_kv_off, plan->qtile_seg, plan->qtile_q0, plan->n_qtiles, H, Hkv, s);
             ppk::gemm_bf16(ppk::kResidual, attn, hd, w->wo[l], hd, x, d, T, d, hd, plan->mtile_m0, plan->n_mtiles, s);
         } else {
-            float* qkv32 = static_cast<float*>(qkv);
-            ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->wqkv[l]), d,
-                          qkv32, qkv_w, T, qkv_w, d, s);
-            ppk::rope_apply(dt, qkv, qkv_w, table, plan->slot_pos, plan->slot_seg, T, H + Hkv, D, s);
-            ppk::kv_scatter(dt, qkv, qkv_w, hd, kvw, kc, vc, plan->slot_kv, T, s);
+            float* qkv32 = static_cast<float*>(qkv);   // the queries, in rows of the whole projection's width
+            const ppk::QkvOut qo{qkv, qkv_w, kc, vc, kvw, table, plan->slot_pos, plan->slot_kv, H, Hkv};
+            ppk::qkv_rope_f32(static_cast<const float*>(xn), d, static_cast<const float*>(w->wqkv[l]), d, T, d, D, qo, s);
             ppk::attention_f32(qkv32, qkv_w, static_cast<const float*>(kc), static_cast<const float*>(vc), kvw,
                                static_cast<float*>(attn), hd, plan->slot_seg, plan->seg_prompt, plan->seg_start,
                                plan->prompt_kv_off, T, H, Hkv, D, s);
@@ -209,9 +204,8 @@ extern "C" pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const
                            s);
             ppk::gemm_bf16(ppk::kResidual, act, F, w->w_down[l], F, x, d, T, d, F, plan->mtile_m0, plan->n_mtiles, s);
         } else {
-            ppk::gemm_f32(ppk::kStore, static_cast<const float*>(xn), d, static_cast<const float*>(w->w_gateup[l]), d,
-                          gu, 2 * F, T, 2 * F, d, s);
-            ppk::swiglu_f32(gu, static_cast<float*>(act), T, F, s);
+            ppk::gemm_f32(ppk::kSwiGLU, static_cast<const float*>(xn), d, static_cast<const float*>(w->w_gateup[l]), d,
+                          static_cast<float*>(act), F, T, 2 * F, d, s);
             ppk::gemm_f32(ppk::kResidual, static_cast<const float*>(act), F, static_cast<const float*>(w->w_down[l]),
                           F, x, d, T, d, F, s);
         }

@@ -68,6 +68,20 @@ def test_tiny_fp32_workload_meets_bar(seed, padded):
         assert mx <= BAR_MAX and mean <= BAR_MEAN
 
 
+@pytest.mark.parametrize("H,Hkv,Dh", [(2, 1, 128), (4, 2, 64)])
+def test_fp32_fused_qkv_head_sizes(H, Hkv, Dh):
+    """The float32 QKV projection's fused RoPE and cache stores at both head sizes, grouped
+    query, with row-tail pads; packed and padded bit-identical."""
+    case = W.make_case(1, 4, lengths=np.array([70, 3, 40, 1]), capacity=100, random_gains=True, n_layers=2,
+                       n_heads=H, n_kv_heads=Hkv, head_dim=Dh, ffn_dim=304)
+    packed = gpu_prefill(case, pp.pp_pack(case.lengths, case.capacity))
+    padded = gpu_prefill(case, pp.pp_pack_padded(case.lengths))
+    for mx, mean in _check_bar(f"f32 H{H}/{Hkv} D{Dh}", packed, _oracle(case), 2):
+        assert mx <= 1e-4 and mean <= 1e-5
+    for a, b in zip([packed[0], *packed[1], *packed[2]], [padded[0], *padded[1], *padded[2]]):
+        assert np.array_equal(a, b)
+
+
 def test_tiny_fp32_deeper_model():
     case = W.make_case(1, 3, n_layers=3, random_gains=True, k=12)
     gpu = gpu_prefill(case, pp.pp_pack(case.lengths, case.capacity))

@@ -188,6 +188,27 @@ def test_gemm_f32():
     assert mx <= 1e-4
 
 
+@pytest.mark.parametrize("M,N,K,ldc", [(1, 1, 16, 1), (32, 32, 32, 32), (33, 20, 48, 20), (31, 33, 80, 37),
+                                       (384, 256, 688, 256), (70, 1376, 256, 1380)])
+@pytest.mark.parametrize("epi", [pp.PP_EPI_STORE, pp.PP_EPI_RESIDUAL])
+def test_gemm_f32_tiles(M, N, K, ldc, epi):
+    """Tile edges, fewer K-steps than the workgroup's four wavefronts, rows of C that are not
+    16-byte aligned; columns past N and rows past M keep what they held."""
+    rng = np.random.default_rng([M, N, K, ldc])
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    B = rng.standard_normal((N, K)).astype(np.float32)
+    C0 = rng.standard_normal((M + 1, ldc)).astype(np.float32)
+    C = f32_dev(C0)
+    pp.pp_gemm(pp.PP_F32, epi, f32_dev(A), K, f32_dev(B), K, C, ldc, M, N, K)
+    got = host64(C)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    if epi == pp.PP_EPI_RESIDUAL:
+        ref += C0[:M, :N]
+    bound = (K + 4) * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(B).T + 4)   # any order of float32 sums
+    assert np.all(np.abs(got[:M, :N] - ref) <= bound)
+    assert np.array_equal(got[:M, N:], C0[:M, N:]) and np.array_equal(got[M], C0[M])
+
+
 # ----------------------------------------------------------------------------- attention
 ATTN_CASES = [
     # lengths, capacity, H, Hkv  (segments shorter / longer than a tile, ragged tails, rows with pads)
@@ -290,6 +311,22 @@ def test_attention_f32(padded):
     real = plan.slot_kv >= 0
     mx, _ = report(f"attention f32 padded={padded}", host64(out)[real], ref[real])
     assert mx <= 1e-5
+
+
+@pytest.mark.parametrize("padded", [False, True])
+@pytest.mark.parametrize("lengths,H,Hkv,Dh", [([1, 63, 64, 65, 72, 130], 4, 2, 64), ([129, 7, 200], 2, 1, 128)])
+def test_attention_f32_key_tiles(lengths, H, Hkv, Dh, padded):
+    """Prompts around and past a 64-key tile, both head sizes, spans with keys past the prompt."""
+    plan = pp.pp_pack_padded(lengths) if padded else pp.pp_pack(lengths, max(lengths) + 30)
+    rng = np.random.default_rng([sum(lengths), H, Dh])
+    q, kc, vc = _attn_inputs(plan, rng, H, Hkv, Dh, 1.0, pp.PP_F32)
+    out = torch.full((plan.n_slots, H * Dh), float("nan"), dtype=torch.float32, device="cuda")
+    pp.pp_attention(_cfg(H, Hkv, d=256, F=688, dtype=pp.PP_F32, D_=Dh), pp.DevicePlan(plan), f32_dev(q), H * Dh,
+                    f32_dev(kc), f32_dev(vc), out)
+    got, ref = host64(out), _attn_ref(plan, q, kc, vc, H, Hkv, Dh)
+    span = plan.slot_seg >= 0
+    assert np.all(np.isnan(got[~span]))
+    assert report(f"attention f32 {lengths} padded={padded}", got[span], ref[span])[0] <= 1e-5
 
 
 # ----------------------------------------------------------------------------- fused QKV projection
