@@ -5,7 +5,7 @@
 // m + n_new slots).  pp_decode_step validates everything, carves the caller's workspace and
 // enqueues, without host synchronisation:
 //
-//   decode_prep (positions, RoPE rows, append rows); embed of the k fed tokens
+//   start: positions, RoPE rows, append rows; embedding of the k fed tokens and the first norm
 //   per layer: rmsnorm -> QKV projection with RoPE and the append to the generation cache
 //              (the prefill's fused epilogue) ->
 //              split-key decode attention + combine -> O GEMM (+residual) -> rmsnorm ->
@@ -178,8 +178,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
     float2* table = reinterpret_cast<float2*>(ws + L.table);
     int32_t* slot_pos = reinterpret_cast<int32_t*>(ws + L.ints);
     int32_t* slot_kv = slot_pos + k;
-    int32_t* slot_seg = slot_kv + k;
-    int32_t* ident = slot_seg + k;        // k + 1 entries
+    int32_t* ident = slot_kv + k;         // k + 1 entries
     const size_t ctx_layer = size_t(g->ctx_rows) * kvw * e, gen_layer = size_t(g->gen_rows) * kvw * e;
     // the prompts' context chunks together: at most ceil(ctx_rows / chunk) + k, as every prompt's
     // span lies in its own ctx_rows (and at most k x the longest prompt's)
@@ -201,14 +200,14 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
             ppk::rmsnorm(out_dtype, x, gain, out, k, d, eps, s);
         pending = 0;
     };
-    ppk::decode_prep(Ly, step, D, cfg->rope_theta, table, slot_pos, slot_kv, slot_seg, ident, s);
-    ppk::embed(dt, x, w->embed, cfg->vocab, tokens_in, ident, k, d, s);
+    ppk::decode_start(dt, Ly, step, D, cfg->rope_theta, table, slot_pos, slot_kv, ident, x, w->embed, cfg->vocab,
+                      tokens_in, d, w->attn_norm[0], xn, eps, s);
     for (int l = 0; l < cfg->n_layers; ++l) {
         const void* ck = static_cast<const char*>(ctx_k) + l * ctx_layer;
         const void* cv = static_cast<const char*>(ctx_v) + l * ctx_layer;
         void* gk = static_cast<char*>(gen_k) + l * gen_layer;
         void* gv = static_cast<char*>(gen_v) + l * gen_layer;
-        norm(w->attn_norm[l], xn, dt);
+        if (l > 0) norm(w->attn_norm[l], xn, dt);
         if (plan.mode == kStream) {
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
             ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,

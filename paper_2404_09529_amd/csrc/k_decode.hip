@@ -3,10 +3,6 @@
 // decoder (section 2.2: one forward pass per token, earlier keys and values read from the
 // cache).
 //
-// decode_prep_kernel     per prompt: the token's position pos0 + step (restart positions,
-//                        section 3.2, continued into generation), cos/sin of that position
-//                        for RoPE (evaluated in float64 as in the prefill's table), the
-//                        generation-cache row the step appends to, and identity indices.
 // decode_attn_kernel     split-key attention of one query row per prompt against that
 //                        prompt's keys only: context rows (its prompt tokens, plus masked
 //                        padding in the full-batching layout) and the generated rows so far.
@@ -54,28 +50,6 @@ namespace {
 constexpr int CH = ppk::kDecodeChunk;   // keys per chunk: 4 wavefronts x IT iterations x 8 keys
 constexpr int IT = CH / 32;
 constexpr float kLog2e = 1.4426950408889634f;
-
-__global__ __launch_bounds__(64) void decode_prep_kernel(int k, int step, const int32_t* __restrict__ pos0,
-                                                         const int32_t* __restrict__ gen_off, int D, double theta,
-                                                         float2* __restrict__ table, int32_t* __restrict__ slot_pos,
-                                                         int32_t* __restrict__ slot_kv, int32_t* __restrict__ slot_seg,
-                                                         int32_t* __restrict__ ident) {
-    const int i = blockIdx.x, j = threadIdx.x;
-    if (i >= k) return;
-    const int half = D / 2;
-    if (j < half) {
-        const double inv_freq = pow(theta, -2.0 * j / static_cast<double>(D));
-        const double a = static_cast<double>(pos0[i] + step) * inv_freq;
-        table[int64_t(i) * half + j] = make_float2(static_cast<float>(cos(a)), static_cast<float>(sin(a)));
-    }
-    if (j == 0) {
-        slot_pos[i] = i;                 // row i of this step's table
-        slot_kv[i] = gen_off[i] + step;  // the row this step appends to
-        slot_seg[i] = 0;
-        ident[i] = i;
-        if (i == k - 1) ident[k] = k;
-    }
-}
 
 template <typename T, int DL>
 __device__ __forceinline__ void load_slice(const T* p, float* v) {
@@ -992,12 +966,6 @@ void attn_dispatch(int D, int R, const void* q, int64_t ldq, const void* ctx_k, 
 }  // namespace
 
 namespace ppk {
-
-void decode_prep(const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
-                 int32_t* slot_kv, int32_t* slot_seg, int32_t* ident, hipStream_t s) {
-    decode_prep_kernel<<<Ly.k, 64, 0, s>>>(Ly.k, step, Ly.pos0, Ly.gen_off, D, static_cast<double>(theta), table,
-                                           slot_pos, slot_kv, slot_seg, ident);
-}
 
 void decode_attention(int dtype, const void* q, int64_t ldq, const void* ctx_k, const void* ctx_v,
                       const void* gen_k, const void* gen_v, int64_t ldkv, const DecodeLayout& Ly, int step, int H,

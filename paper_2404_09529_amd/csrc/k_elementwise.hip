@@ -18,14 +18,16 @@ template <typename T>
 T* at(void* p) { return static_cast<T*>(p); }
 
 // ------------------------------------------------------------------------------- RoPE table
+__device__ __forceinline__ float2 rope_entry(int64_t position, int i, int D, double theta) {
+    const double inv_freq = pow(theta, -2.0 * i / static_cast<double>(D));
+    const double a = static_cast<double>(position) * inv_freq;
+    return make_float2(static_cast<float>(cos(a)), static_cast<float>(sin(a)));
+}
+
 __global__ void rope_table_kernel(float2* __restrict__ table, int64_t n, int half, int D, double theta) {
     const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= n) return;
-    const int64_t p = idx / half;
-    const int i = static_cast<int>(idx % half);
-    const double inv_freq = pow(theta, -2.0 * i / static_cast<double>(D));
-    const double a = static_cast<double>(p) * inv_freq;
-    table[idx] = make_float2(static_cast<float>(cos(a)), static_cast<float>(sin(a)));
+    table[idx] = rope_entry(idx / half, static_cast<int>(idx % half), D, theta);
 }
 
 // ------------------------------------------------------------------------------- embedding
@@ -91,7 +93,14 @@ __device__ __forceinline__ void store4(bf16* p, f32x4 v) {
     *reinterpret_cast<bf16x4*>(p) = b;
 }
 
-// NC > 0: d == NC * 256, the row is held in registers (one read of x).  NC == 0: any d that
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16* p) {
+    const bf16x4 b = *reinterpret_cast<const bf16x4*>(p);
+    return f32x4{static_cast<float>(b[0]), static_cast<float>(b[1]), static_cast<float>(b[2]), static_cast<float>(b[3])};
+}
+
+// NC > 0: d == NC * 256, the row is held in registers (one read of x; d = 5120 without it, 2815
+// rows: 31 us, 25 with it).  NC == 0: any d that
 // is a multiple of 4, two passes over the row.
 template <typename TO, int NC, bool UNPACK>
 __global__ __launch_bounds__(kBlock) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ g,
@@ -151,10 +160,118 @@ void rmsnorm_dispatch(const float* x, const float* g, TO* out, const int32_t* sl
         case 4: PP_RMS(4); break;
         case 8: PP_RMS(8); break;
         case 16: PP_RMS(16); break;
+        case 20: PP_RMS(20); break;
         case 32: PP_RMS(32); break;
         default: PP_RMS(0); break;
     }
 #undef PP_RMS
+}
+
+// ------------------------------------------------------------------------------- start
+// The first launch of a prefill or a decode step: the RoPE table, the embedding gather and the
+// first layer's RMSNorm.  They are independent or share a row, and a launch of its own costs each
+// about 4.7 us; the norm takes the row from registers instead of reading x back (7B, 27,721
+// tokens: 115 + 115 -> 150 us).  The first table_blocks workgroups fill the table, the others take
+// kRowsPerBlock rows each.  A lane's share of a row and the order of the sum are rmsnorm_kernel's,
+// so xn is the same bit for bit.
+struct TableArgs {
+    float2* table;
+    int64_t n;              // entries
+    int half, D;
+    double theta;
+    // a decode step's rows: table row i is position pos0[i] + step, and the step's per-prompt
+    // indices are written beside it (see decode_start); null for a table of positions 0, 1, ..
+    const int32_t *pos0, *gen_off;
+    int step;
+    int32_t *slot_pos, *slot_kv, *ident;
+};
+
+template <typename TE, int NC>
+__global__ __launch_bounds__(kBlock) void start_kernel(float* __restrict__ x, const TE* __restrict__ E,
+                                                       const int32_t* __restrict__ tokens,
+                                                       const int32_t* __restrict__ slot_kv, int T, int d, int vocab,
+                                                       const float* __restrict__ g, TE* __restrict__ xn, float eps,
+                                                       unsigned table_blocks, TableArgs ta) {
+    if (blockIdx.x < table_blocks) {
+        const int64_t idx = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+        if (idx >= ta.n) return;
+        const int64_t p = idx / ta.half;
+        const int i = static_cast<int>(idx % ta.half);
+        ta.table[idx] = rope_entry(ta.pos0 ? int64_t(ta.pos0[p]) + ta.step : p, i, ta.D, ta.theta);
+        if (ta.pos0 && i == 0) {
+            const int m = static_cast<int>(p);
+            ta.slot_pos[m] = m;                          // row m of this step's table
+            ta.slot_kv[m] = ta.gen_off[m] + ta.step;     // the row this step appends to
+            ta.ident[m] = m;
+            if ((p + 1) * ta.half == ta.n) ta.ident[m + 1] = m + 1;
+        }
+        return;
+    }
+    const int lane = threadIdx.x % kWave;
+    const int64_t row = int64_t(blockIdx.x - table_blocks) * kRowsPerBlock + threadIdx.x / kWave;
+    if (row >= T) return;
+    const int64_t kv = slot_kv ? slot_kv[row] : row;
+    int tok = kv < 0 ? -1 : tokens[kv];
+    if (tok >= vocab) tok = -1;   // as a pad slot: a zero vector, whose norm is zero (row 0 is read)
+    const TE* er = E + int64_t(max(tok, 0)) * d;
+    float* xr = x + row * d;
+    TE* yr = xn + row * d;
+    float ss = 0.f;
+    if constexpr (NC > 0) {
+        f32x4 v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = load4(er + c * 256 + lane * 4);
+        if (tok < 0) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[c] = f32x4{};
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            store4(xr + c * 256 + lane * 4, v[c]);
+            ss += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
+        }
+        ss = wave_sum(ss);
+        const float scale = rsqrtf(ss / static_cast<float>(d) + eps);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const f32x4 gg = *reinterpret_cast<const f32x4*>(g + c * 256 + lane * 4);
+            store4(yr + c * 256 + lane * 4, v[c] * scale * gg);
+        }
+    } else {
+        for (int c = lane * 4; c < d; c += 256) {
+            const f32x4 v = tok < 0 ? f32x4{} : load4(er + c);
+            store4(xr + c, v);
+            ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+        }
+        ss = wave_sum(ss);
+        const float scale = rsqrtf(ss / static_cast<float>(d) + eps);
+        for (int c = lane * 4; c < d; c += 256) {
+            const f32x4 v = tok < 0 ? f32x4{} : load4(er + c);
+            const f32x4 gg = *reinterpret_cast<const f32x4*>(g + c);
+            store4(yr + c, v * scale * gg);
+        }
+    }
+}
+
+template <typename TE>
+void start_dispatch(float* x, const TE* E, const int32_t* tokens, const int32_t* slot_kv, int T, int d, int vocab,
+                    const float* g, TE* xn, float eps, const TableArgs& ta, hipStream_t s) {
+    const unsigned tb = static_cast<unsigned>((ta.n + kBlock - 1) / kBlock);
+    const unsigned grid = tb + (T + kRowsPerBlock - 1) / kRowsPerBlock;
+    if (grid == 0) return;
+    const int nc = d % 256 == 0 ? d / 256 : 0;
+#define PP_START(NC) start_kernel<TE, NC><<<grid, kBlock, 0, s>>>(x, E, tokens, slot_kv, T, d, vocab, g, xn, eps, tb, ta)
+    switch (nc) {
+        case 1: PP_START(1); break;
+        case 2: PP_START(2); break;
+        case 4: PP_START(4); break;
+        case 8: PP_START(8); break;
+        case 16: PP_START(16); break;
+        case 20: PP_START(20); break;
+        case 32: PP_START(32); break;
+        default: PP_START(0); break;
+    }
+#undef PP_START
 }
 
 // ------------------------------------------------------------------------------- RoPE
@@ -218,6 +335,28 @@ void rope_table(float2* table, int P, int D, float theta, hipStream_t s) {
     const int64_t n = int64_t(P) * (D / 2);
     if (n == 0) return;
     rope_table_kernel<<<blocks_for(n), kBlock, 0, s>>>(table, n, D / 2, D, static_cast<double>(theta));
+}
+
+void prefill_start(int dtype, float2* table, int P, int D, float theta, float* x, const void* E, int vocab,
+                   const int32_t* tokens, const int32_t* slot_kv, int T, int d, const float* g, void* xn, float eps,
+                   hipStream_t s) {
+    const TableArgs ta{table, int64_t(P) * (D / 2), D / 2, D, static_cast<double>(theta), nullptr, nullptr, 0,
+                       nullptr, nullptr, nullptr};
+    if (dtype == PP_BF16)
+        start_dispatch(x, static_cast<const bf16*>(E), tokens, slot_kv, T, d, vocab, g, at<bf16>(xn), eps, ta, s);
+    else
+        start_dispatch(x, static_cast<const float*>(E), tokens, slot_kv, T, d, vocab, g, at<float>(xn), eps, ta, s);
+}
+
+void decode_start(int dtype, const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
+                  int32_t* slot_kv, int32_t* ident, float* x, const void* E, int vocab, const int32_t* tokens, int d,
+                  const float* g, void* xn, float eps, hipStream_t s) {
+    const TableArgs ta{table, int64_t(Ly.k) * (D / 2), D / 2, D, static_cast<double>(theta), Ly.pos0, Ly.gen_off, step,
+                       slot_pos, slot_kv, ident};
+    if (dtype == PP_BF16)
+        start_dispatch(x, static_cast<const bf16*>(E), tokens, nullptr, Ly.k, d, vocab, g, at<bf16>(xn), eps, ta, s);
+    else
+        start_dispatch(x, static_cast<const float*>(E), tokens, nullptr, Ly.k, d, vocab, g, at<float>(xn), eps, ta, s);
 }
 
 void embed(int dtype, float* x, const void* E, int vocab, const int32_t* tokens, const int32_t* slot_kv, int T,

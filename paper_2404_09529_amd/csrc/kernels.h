@@ -10,6 +10,11 @@ namespace ppk {
 // cos/sin(p * theta^(-2i/D)) for p < P, i < D/2, evaluated in float64, stored float2 [P][D/2].
 void rope_table(float2* table, int P, int D, float theta, hipStream_t s);
 
+// The first launch of a prefill: rope_table, embed and the first layer's rmsnorm into xn.
+void prefill_start(int dtype, float2* table, int P, int D, float theta, float* x, const void* E, int vocab,
+                   const int32_t* tokens, const int32_t* slot_kv, int T, int d, const float* g, void* xn, float eps,
+                   hipStream_t s);
+
 // x[t] = E[tokens[slot_kv[t]]] (float32), or 0 where slot_kv[t] < 0 or the id is not in [0, vocab).
 void embed(int dtype, float* x, const void* E, int vocab, const int32_t* tokens, const int32_t* slot_kv,
            int T, int d, hipStream_t s);
@@ -117,11 +122,13 @@ struct DecodeLayout {
     const int32_t *ctx_off, *ctx_span, *ctx_valid, *pos0, *gen_off;
 };
 
-// Per prompt i < k for decode step `step`: table[i] = cos/sin((pos0[i] + step) theta^(-2j/D))
-// for j < D/2 (float64, float2 [k][D/2]); slot_pos[i] = i; slot_kv[i] = gen_off[i] + step;
-// slot_seg[i] = 0; ident[i] = i for i <= k (k + 1 entries).
-void decode_prep(const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
-                 int32_t* slot_kv, int32_t* slot_seg, int32_t* ident, hipStream_t s);
+// The first launch of a decode step.  Per prompt i < k: table[i] = cos/sin((pos0[i] + step)
+// theta^(-2j/D)) for j < D/2 (float64, float2 [k][D/2]); slot_pos[i] = i; slot_kv[i] = gen_off[i] +
+// step; ident[i] = i for i <= k (k + 1 entries); x[i] = E[tokens[i]] (float32; 0 for an id not in
+// [0, vocab)) and xn[i] = RMSNorm(x[i]) * g in dtype.
+void decode_start(int dtype, const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
+                  int32_t* slot_kv, int32_t* ident, float* x, const void* E, int vocab, const int32_t* tokens, int d,
+                  const float* g, void* xn, float eps, hipStream_t s);
 
 // The decode attention's per-chunk results (k x H x n_chunks x (D + 4) float32: o[D], max,
 // sum) and what is needed to merge a prompt's chunks.

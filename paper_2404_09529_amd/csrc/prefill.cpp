@@ -3,7 +3,7 @@
 // Host side only: validates every argument, carves the caller's workspace, and enqueues
 // the kernel sequence on the caller's stream without any host synchronisation:
 //
-//   rope_table; embed (TENSORIZE through the slot map)
+//   start: RoPE table, embedding (TENSORIZE through the slot map), the first layer's rmsnorm
 //   per layer: rmsnorm -> QKV projection with RoPE at restart positions and the KV UNPACK
 //              fused into its epilogue -> attention under the independent mask, keys and values read
 //              from the caches -> O GEMM (+residual) -> rmsnorm -> gate/up GEMM with
@@ -176,12 +176,12 @@ extern "C" pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const
     float2* table = reinterpret_cast<float2*>(ws + L.table);
     const size_t cache_layer_bytes = size_t(plan->total_len) * kvw * e;
 
-    ppk::rope_table(table, plan->max_len, D, cfg->rope_theta, s);
-    ppk::embed(dt, x, w->embed, cfg->vocab, tokens, plan->slot_kv, T, d, s);
+    ppk::prefill_start(dt, table, plan->max_len, D, cfg->rope_theta, x, w->embed, cfg->vocab, tokens, plan->slot_kv, T, d,
+                       w->attn_norm[0], xn, eps, s);
     for (int l = 0; l < cfg->n_layers; ++l) {
         void* kc = static_cast<char*>(k_cache) + l * cache_layer_bytes;
         void* vc = static_cast<char*>(v_cache) + l * cache_layer_bytes;
-        ppk::rmsnorm(dt, x, w->attn_norm[l], xn, T, d, eps, s);
+        if (l > 0) ppk::rmsnorm(dt, x, w->attn_norm[l], xn, T, d, eps, s);
         if (bf) {
             const ppk::QkvOut qo{qkv, hd, kc, vc, kvw, table, plan->slot_pos, plan->slot_kv, H, Hkv};
             ppk::qkv_rope_bf16(xn, d, w->wqkv[l], d, T, d, plan->mtile_m0, plan->n_mtiles, qo, s);
