@@ -90,7 +90,9 @@ __device__ __forceinline__ void merge(float& m, float& l, float* o, float m2, fl
 }
 
 // One (prompt i, key/value head g, chunk c) of the decode attention: the chunk's (max, sum,
-// output) for the group's R query heads into part.
+// output) for the group's R query heads into part.  The float32 form: lane l of wavefront w has key
+// group kg = l / 8 (one key per iteration) and dimension slice dl = l % 8 (D / 8 consecutive
+// elements); keys of the chunk: j0 + 8 IT w + 8 it + kg.
 template <typename T, int D, int R>
 __device__ __forceinline__ void decode_attn_chunk(
     const T* __restrict__ q, int64_t ldq, const T* __restrict__ ctx_k, const T* __restrict__ ctx_v,
@@ -225,6 +227,159 @@ __device__ __forceinline__ void decode_attn_chunk(
     __syncthreads();   // red is reused by the workgroup's next item
 }
 
+// The bf16 form (head dim 128): wavefront w takes keys 32 w .. + 31 of the chunk.  The scores of
+// its two blocks of 16 keys are 16x16x32 MFMAs with the group's R queries as the other operand's
+// rows (rows past R are zero: the matrix cores are idle otherwise), so lane l holds key l % 16's
+// scores for queries 4 (l / 16) + 0..3 with no reduction per key; one maximum and one sum per query
+// across 16 lanes; the probabilities (float32) go through LDS to the lanes that accumulate the
+// values: lane l takes dims 8 (l % 16) .. + 7 of keys 4 it + l / 16.  Against a shuffled dot product
+// per key and query: 48 prompts of a 32/8-head layer, 43 MB of keys and values, 35 -> 20 us;
+// 150 prompts of 16 heads, 354 MB, 92 -> 90.
+template <int R>
+__device__ __forceinline__ void decode_attn_chunk_bf16(
+    const bf16* __restrict__ q, int64_t ldq, const bf16* __restrict__ ctx_k, const bf16* __restrict__ ctx_v,
+    const bf16* __restrict__ gen_k, const bf16* __restrict__ gen_v, int64_t ldkv, const int32_t* __restrict__ ctx_off,
+    const int32_t* __restrict__ ctx_span, const int32_t* __restrict__ ctx_valid, const int32_t* __restrict__ gen_off,
+    int step, int Hkv, int n_ctx_chunks, int n_chunks, float* __restrict__ part, int i, int g, int c) {
+    constexpr int D = 128, PS = D + 4;
+    __shared__ __attribute__((aligned(16))) float prob[4][32][R];
+    __shared__ __attribute__((aligned(16))) float red[4][R][D + 4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lr = lane & 15, q4 = lane >> 4;
+    const bf16* K;
+    const bf16* V;
+    int64_t row0;
+    int j0, jend, valid;
+    if (c < n_ctx_chunks) {
+        j0 = c * CH;
+        jend = min(j0 + CH, ctx_span[i]);
+        valid = ctx_valid[i];
+        row0 = ctx_off[i];
+        K = ctx_k;
+        V = ctx_v;
+    } else {
+        j0 = (c - n_ctx_chunks) * CH;
+        jend = min(j0 + CH, step + 1);
+        valid = step + 1;
+        row0 = gen_off[i];
+        K = gen_k;
+        V = gen_v;
+    }
+    if (j0 >= jend) return;              // generated keys not there yet: no partial, never combined
+
+    // every key and value of the wavefront requested before the first use (rows past the chunk
+    // read as its last row, then ignored): the memory latency is paid once
+    const int jw = j0 + 32 * w;
+    const int64_t col = int64_t(g) * D;
+    u32x4 kraw[2][4], vraw[8], qraw[4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const bf16* kr = K + (row0 + min(jw + 16 * b + lr, jend - 1)) * ldkv + col + 8 * q4;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) kraw[b][st] = *reinterpret_cast<const u32x4*>(kr + 32 * st);
+    }
+#pragma unroll
+    for (int it = 0; it < 8; ++it)
+        vraw[it] = *reinterpret_cast<const u32x4*>(V + (row0 + min(jw + 4 * it + q4, jend - 1)) * ldkv + col + 8 * lr);
+    const bf16* qr = q + int64_t(i) * ldq + int64_t(g * R + min(lr, R - 1)) * D + 8 * q4;
+#pragma unroll
+    for (int st = 0; st < 4; ++st) qraw[st] = *reinterpret_cast<const u32x4*>(qr + 32 * st);
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        asm volatile("" : "+v"(kraw[0][st]), "+v"(kraw[1][st]), "+v"(qraw[st]));
+        asm volatile("" : "+v"(vraw[2 * st]), "+v"(vraw[2 * st + 1]));
+    }
+    f32x4 sc[2] = {};
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        const bf16x8 qf = lr < R ? __builtin_bit_cast(bf16x8, qraw[st]) : bf16x8{};
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            sc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf, __builtin_bit_cast(bf16x8, kraw[b][st]), sc[b], 0, 0, 0);
+    }
+    // lane l: scores of key jw + 16 b + l % 16 for queries 4 (l / 16) + e, in base 2; padding of the
+    // full-batching layout is read, then masked
+    constexpr int NE = R < 4 ? R : 4;
+    const float scale = kLog2e * rsqrtf(static_cast<float>(D));
+    float m[NE], l[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int j = jw + 16 * b + lr;
+            sc[b][e] = j < jend && j < valid ? sc[b][e] * scale : -INFINITY;
+        }
+        m[e] = fmaxf(sc[0][e], sc[1][e]);
+#pragma unroll
+        for (int x = 1; x < 16; x <<= 1) m[e] = fmaxf(m[e], __shfl_xor(m[e], x));
+        const float mm = m[e] == -INFINITY ? 0.f : m[e];   // no key: every probability 0
+        float p[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) p[b] = exp2f(sc[b][e] - mm);
+        l[e] = p[0] + p[1];
+#pragma unroll
+        for (int x = 1; x < 16; x <<= 1) l[e] += __shfl_xor(l[e], x);
+        if (4 * q4 + e < R) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) prob[w][16 * b + lr][4 * q4 + e] = p[b];
+        }
+        if (lr == 0 && 4 * q4 + e < R) {
+            red[w][4 * q4 + e][D] = m[e];
+            red[w][4 * q4 + e][D + 1] = l[e];
+        }
+    }
+    __builtin_amdgcn_wave_barrier();   // a wavefront's own LDS writes and reads stay in order
+    float o[R][8];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+        const float* pk = prob[w][4 * it + q4];
+        float p[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r] = pk[r];
+        const int j = jw + 4 * it + q4;
+        // rows that are no key may hold anything: not a number times 0 must not enter
+        const bf16x8 vv = j < jend && j < valid ? __builtin_bit_cast(bf16x8, vraw[it]) : bf16x8{};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = static_cast<float>(vv[e]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) o[r][e] = fmaf(p[r], v, o[r][e]);
+        }
+    }
+    // the 4 key groups of the wavefront (one maximum for all), then the 4 wavefronts
+#pragma unroll
+    for (int x = 16; x < 64; x <<= 1)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[r][e] += __shfl_xor(o[r][e], x);
+    if (q4 == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            *reinterpret_cast<f32x4*>(&red[w][r][8 * lr]) = f32x4{o[r][0], o[r][1], o[r][2], o[r][3]};
+            *reinterpret_cast<f32x4*>(&red[w][r][8 * lr + 4]) = f32x4{o[r][4], o[r][5], o[r][6], o[r][7]};
+        }
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < R * D; idx += 256) {
+        const int r = idx / D, e = idx % D;
+        float mm = red[0][r][D], ll = red[0][r][D + 1], oo = red[0][r][e];
+#pragma unroll
+        for (int w2 = 1; w2 < 4; ++w2) merge<1>(mm, ll, &oo, red[w2][r][D], red[w2][r][D + 1], &red[w2][r][e]);
+        float* pp = part + ((int64_t(i) * (Hkv * R) + g * R + r) * n_chunks + c) * PS;
+        pp[e] = oo;
+        if (e == 0) {
+            pp[D] = mm;
+            pp[D + 1] = ll;
+        }
+    }
+    __syncthreads();   // prob and red are reused by the workgroup's next item
+}
+
 // The decode attention's work list: first the generated keys' chunks of every prompt
 // (k x n_gen_chunks, prompt-major), then each prompt's context chunks, prompt by prompt
 // (ceil(ctx_span / CH) each).  Item -> (prompt, chunk index into the partial results); an
@@ -255,36 +410,38 @@ __device__ __forceinline__ int2 attn_item(int item, int k, int n_gen_chunks, int
     return make_int2(-1, 0);
 }
 
-// Lane l of wavefront w: key group kg = l / 8 (one key per iteration), dimension slice
-// dl = l % 8 (D / 8 consecutive elements).  Keys of the chunk: j0 + 8 IT w + 8 it + kg.
 // list == 0: workgroup (i Hkv + g, c) takes chunk c of prompt i and key/value head g, every
 // prompt n_ctx_chunks + n_gen_chunks of them (those past its keys return at once).
 // list != 0: workgroup (g, y) takes the work-list items y, y + gridDim.y, ... of head g (one
 // each when the grid holds them all), so only real chunks occupy the CUs: a batch of nine
 // 1-token prompts and one of 1000 at the 7B shape, 10.4 -> 10.0 us.  The host takes the list
 // when it is shorter; in the full-batching layout it is not, and the lookup would cost each
-// workgroup a dependent load (1.3B: 2% of the step).  bf16 with one query head per key/value
-// head: four workgroups per CU (at most 128 registers), as the chunks are latency-bound (at
-// 129 registers, three per CU, the 7B batch above took 11.6 us); the other forms would spill.
+// workgroup a dependent load (1.3B: 2% of the step).  Workgroups per CU: as many as the registers
+// allow without spilling, as the chunks are latency-bound.
 template <typename T, int D, int R>
-__global__ __launch_bounds__(256, (R == 1 && sizeof(T) == 2) ? 4 : 1) void decode_attn_kernel(
+__global__ __launch_bounds__(256, sizeof(T) == 2 ? (R <= 2 ? 4 : R == 4 ? 3 : 2) : 1) void decode_attn_kernel(
     const T* __restrict__ q, int64_t ldq, const T* __restrict__ ctx_k, const T* __restrict__ ctx_v,
     const T* __restrict__ gen_k, const T* __restrict__ gen_v, int64_t ldkv, const int32_t* __restrict__ ctx_off,
     const int32_t* __restrict__ ctx_span, const int32_t* __restrict__ ctx_valid, const int32_t* __restrict__ gen_off,
     int step, int k, int Hkv, int n_ctx_chunks, int n_gen_chunks, int list, float* __restrict__ part) {
     const int n_chunks = n_ctx_chunks + n_gen_chunks;
+    auto run = [&](int i, int g, int c) {
+        if constexpr (sizeof(T) == 2)
+            decode_attn_chunk_bf16<R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
+                                      step, Hkv, n_ctx_chunks, n_chunks, part, i, g, c);
+        else
+            decode_attn_chunk<T, D, R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
+                                       step, Hkv, n_ctx_chunks, n_chunks, part, i, g, c);
+    };
     if (!list) {
-        decode_attn_chunk<T, D, R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
-                                   step, Hkv, n_ctx_chunks, n_chunks, part, blockIdx.x / Hkv, blockIdx.x % Hkv,
-                                   blockIdx.y);
+        run(blockIdx.x / Hkv, blockIdx.x % Hkv, blockIdx.y);
         return;
     }
     for (int item = blockIdx.y;; item += gridDim.y) {
         const int2 ic = attn_item(item, k, n_gen_chunks, n_ctx_chunks, ctx_span);
         const int i = __builtin_amdgcn_readfirstlane(ic.x), c = __builtin_amdgcn_readfirstlane(ic.y);
         if (i < 0) return;
-        decode_attn_chunk<T, D, R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
-                                   step, Hkv, n_ctx_chunks, n_chunks, part, i, blockIdx.x, c);
+        run(i, blockIdx.x, c);
     }
 }
 
@@ -956,7 +1113,7 @@ void attn_dispatch(int D, int R, const void* q, int64_t ldq, const void* ctx_k, 
         if (!out) return;   // the consumer merges the chunks itself
         decode_combine_kernel<T, 128><<<blocks, 256, 0, s>>>(part, Ly.k, H, Ly.ctx_span, step, Ly.n_ctx_chunks, nch,
                                                              static_cast<T*>(out), ldo);
-    } else {
+    } else if constexpr (sizeof(T) == 4) {   // bf16 models have heads of 128
         attn_by_group<T, 64>(R, q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, Ly, step, Hkv, part, s);
         decode_combine_kernel<T, 64><<<blocks, 256, 0, s>>>(part, Ly.k, H, Ly.ctx_span, step, Ly.n_ctx_chunks, nch,
                                                             static_cast<T*>(out), ldo);
