@@ -11,8 +11,7 @@
 //              split-key decode attention + combine -> O GEMM (+residual) -> rmsnorm ->
 //              gate/up GEMM with SwiGLU -> down GEMM (+residual); with the split-K GEMMs
 //              the residual adds of O and down happen in the norm that follows each
-//   final rmsnorm (float32) -> LM head and greedy choice (the first-token kernels, one
-//   row per prompt).
+//   final rmsnorm -> LM head and greedy choice (the first-token kernels, one row per prompt).
 // The projections: for bf16 steps of up to 16 prompts, weight-streaming GEMMs for one row
 // per prompt (QKV and gate/up with their epilogues in the kernel; O and down as split-K
 // partial sums that the next norm adds); up to 256 prompts the prefill's GEMM tiles, O and down
@@ -71,7 +70,7 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.q = take(c->dtype == PP_BF16 ? k * hd * 2 : k * qkv_w * 4);   // bf16: rotated queries only
     L.attn = take(k * hd * e);
     L.act = take(k * F * e);
-    L.h = take(k * d * 4);
+    L.h = take(k * d * 4);   // no longer used; the documented size of a workspace holds it
     L.part = take(k * size_t(c->n_heads) * nch * (D + 4) * 4);
     L.table = take(k * (D / 2) * sizeof(float2));
     L.ints = take((4 * k + 1) * sizeof(int32_t));
@@ -173,12 +172,10 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
     void* q = ws + L.q;
     void* attn = ws + L.attn;
     void* act = ws + L.act;
-    float* h = reinterpret_cast<float*>(ws + L.h);
     float* part = reinterpret_cast<float*>(ws + L.part);
     float2* table = reinterpret_cast<float2*>(ws + L.table);
     int32_t* slot_pos = reinterpret_cast<int32_t*>(ws + L.ints);
     int32_t* slot_kv = slot_pos + k;
-    int32_t* ident = slot_kv + k;         // k + 1 entries
     const size_t ctx_layer = size_t(g->ctx_rows) * kvw * e, gen_layer = size_t(g->gen_rows) * kvw * e;
     // the prompts' context chunks together: at most ceil(ctx_rows / chunk) + k, as every prompt's
     // span lies in its own ctx_rows (and at most k x the longest prompt's)
@@ -193,21 +190,21 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
     // the split-K residual projections (O, down) leave their partial sums in gpart; the next
     // norm adds them to x (pending = their split count) before normalising
     int pending = 0;
-    auto norm = [&](const float* gain, void* out, int out_dtype) {
+    auto norm = [&](const float* gain, void* out) {
         if (split)
-            ppk::residual_rmsnorm(out_dtype, x, gpart, pending, k, d, gain, out, eps, s);
+            ppk::residual_rmsnorm(x, gpart, pending, k, d, gain, out, eps, s);
         else
-            ppk::rmsnorm(out_dtype, x, gain, out, k, d, eps, s);
+            ppk::rmsnorm(dt, x, gain, out, k, d, eps, s);
         pending = 0;
     };
-    ppk::decode_start(dt, Ly, step, D, cfg->rope_theta, table, slot_pos, slot_kv, ident, x, w->embed, cfg->vocab,
+    ppk::decode_start(dt, Ly, step, D, cfg->rope_theta, table, slot_pos, slot_kv, x, w->embed, cfg->vocab,
                       tokens_in, d, w->attn_norm[0], xn, eps, s);
     for (int l = 0; l < cfg->n_layers; ++l) {
         const void* ck = static_cast<const char*>(ctx_k) + l * ctx_layer;
         const void* cv = static_cast<const char*>(ctx_v) + l * ctx_layer;
         void* gk = static_cast<char*>(gen_k) + l * gen_layer;
         void* gv = static_cast<char*>(gen_v) + l * gen_layer;
-        if (l > 0) norm(w->attn_norm[l], xn, dt);
+        if (l > 0) norm(w->attn_norm[l], xn);
         if (plan.mode == kStream) {
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
             ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,
@@ -233,7 +230,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
             ppk::gemm_f32(ppk::kResidual, static_cast<const float*>(attn), hd, static_cast<const float*>(w->wo[l]),
                           hd, x, d, k, d, hd, s);
         }
-        norm(w->mlp_norm[l], xn, dt);
+        norm(w->mlp_norm[l], xn);
         if (plan.mode == kStream) {
             const ppk::QkvOut none{};
             ppk::decode_gemm(ppk::kSwiGLU, xn, d, k, w->w_gateup[l], d, 2 * F, d, gpart,
@@ -256,8 +253,10 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                           F, x, d, k, d, F, s);
         }
     }
-    norm(w->final_norm, h, PP_F32);
-    ppk::first_token(dt, h, ident, k, lm_head, cfg->vocab, d, ws + L.ft, logits, tokens_out, s);
+    // the final norm's rows go straight to where the LM head reads them, in its type: a gather of
+    // them from float32, with the same rounding, was a launch of 4.7 us
+    norm(w->final_norm, ws + L.ft);
+    ppk::next_token(dt, k, lm_head, cfg->vocab, d, ws + L.ft, logits, tokens_out, s);
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 // tile size so that a result does not depend on which of them computed it (the packed and the
 // padded layout of a batch take different ones and agree bit for bit).
 #pragma once
+#include "argmax.h"
 #include "device.h"
 #include "kernels.h"
 
@@ -129,5 +130,52 @@ __device__ __forceinline__ void epilogue_direct(f32x4 (&acc)[NB][MB], void* __re
                 }
             }
         }
+    }
+}
+
+// kLogits: the wavefront's columns are one block of 128 vocabulary rows (NB = 8); rows past the
+// vocabulary V are not reported.
+struct LogitsOut {
+    float* logits;   // [k, V] or null
+    ArgMax* part;    // [k, n_blocks]
+    int V, n_blocks;
+    int vec;         // every row of logits is 16-byte aligned
+};
+template <int MB>
+__device__ __forceinline__ void epilogue_logits(f32x4 (&acc)[8][MB], int k, int mb, int n0, int lane,
+                                                const LogitsOut& lo) {
+    const int lr = lane & 15, g = lane >> 4;
+    if (n0 >= lo.V) return;
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        const int m = mb + 16 * j + lr;
+        f32x4 a[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            asm volatile("" : "+a"(acc[i][j]) : : "memory");
+            a[i] = acc[i][j];
+        }
+        float bv = -INFINITY;
+        int bi = INT32_MAX;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int n = n0 + 16 * i + 4 * g;
+            if (lo.logits && lo.vec && m < k && n < lo.V)
+                *reinterpret_cast<f32x4*>(lo.logits + int64_t(m) * lo.V + n) = a[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (n + e >= lo.V) continue;
+                if (lo.logits && !lo.vec && m < k) lo.logits[int64_t(m) * lo.V + n + e] = a[i][e];
+                if (better(a[i][e], n + e, bv, bi)) { bv = a[i][e]; bi = n + e; }
+            }
+        }
+        // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same prompt
+#pragma unroll
+        for (int x = 16; x < 64; x <<= 1) {
+            const float ov = __shfl_xor(bv, x);
+            const int oi = __shfl_xor(bi, x);
+            if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        }
+        if (g == 0 && m < k) lo.part[int64_t(m) * lo.n_blocks + n0 / 128] = ArgMax{bv, bi};
     }
 }

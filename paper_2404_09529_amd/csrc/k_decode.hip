@@ -1016,10 +1016,10 @@ SegSplit seg_split(int k, int N, int K) {
 // The kernel is latency-bound (k workgroups, a few KB each), so everything it reads (the row,
 // the gains, up to 8 splits' partial sums) is issued before the first wait: one memory round
 // trip where S <= 8 rather than one per split.
-template <typename TO, int E>
+template <int E>
 __global__ __launch_bounds__(1024) void residual_rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ part,
                                                                 int S, int k, int d, const float* __restrict__ g,
-                                                                TO* __restrict__ out, float eps) {
+                                                                bf16* __restrict__ out, float eps) {
     __shared__ float red[16];
     const int m = blockIdx.x, c = 4 * E * threadIdx.x;
     float* xr = x + int64_t(m) * d + c;
@@ -1062,14 +1062,10 @@ __global__ __launch_bounds__(1024) void residual_rmsnorm_kernel(float* __restric
     const float r = rsqrtf(tot / static_cast<float>(d) + eps);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        if constexpr (sizeof(TO) == 2) {
-            bf16x4 o;
+        bf16x4 o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = static_cast<bf16>(v[e][i] * r * gg[e][i]);
-            *reinterpret_cast<bf16x4*>(out + int64_t(m) * d + c + 4 * e) = o;
-        } else {
-            *reinterpret_cast<f32x4*>(out + int64_t(m) * d + c + 4 * e) = v[e] * r * gg[e];
-        }
+        for (int i = 0; i < 4; ++i) o[i] = static_cast<bf16>(v[e][i] * r * gg[e][i]);
+        *reinterpret_cast<bf16x4*>(out + int64_t(m) * d + c + 4 * e) = o;
     }
 }
 
@@ -1150,23 +1146,13 @@ bool decode_stream_ok(int k, int d, int hd, int F) {
     return k >= 1 && k <= 16 && (d == 2048 || d == 4096) && hd % SG_TILE == 0 && F % 128 == 0;
 }
 
-void residual_rmsnorm(int dtype_out, float* x, const float* part, int S, int k, int d, const float* g, void* out,
-                      float eps, hipStream_t s) {
+void residual_rmsnorm(float* x, const float* part, int S, int k, int d, const float* g, void* out, float eps,
+                      hipStream_t s) {
     // whole wavefronts, at most 1024 threads: d % 256 == 0 up to 4096 (4 elements per thread),
     // d % 512 == 0 up to 8192 (8), as residual_rmsnorm_ok checks
-    if (d <= 4096) {
-        const int threads = d / 4;
-        if (dtype_out == PP_BF16)
-            residual_rmsnorm_kernel<bf16, 1><<<k, threads, 0, s>>>(x, part, S, k, d, g, static_cast<bf16*>(out), eps);
-        else
-            residual_rmsnorm_kernel<float, 1><<<k, threads, 0, s>>>(x, part, S, k, d, g, static_cast<float*>(out), eps);
-    } else {
-        const int threads = d / 8;
-        if (dtype_out == PP_BF16)
-            residual_rmsnorm_kernel<bf16, 2><<<k, threads, 0, s>>>(x, part, S, k, d, g, static_cast<bf16*>(out), eps);
-        else
-            residual_rmsnorm_kernel<float, 2><<<k, threads, 0, s>>>(x, part, S, k, d, g, static_cast<float*>(out), eps);
-    }
+    bf16* o = static_cast<bf16*>(out);
+    if (d <= 4096) residual_rmsnorm_kernel<1><<<k, d / 4, 0, s>>>(x, part, S, k, d, g, o, eps);
+    else residual_rmsnorm_kernel<2><<<k, d / 8, 0, s>>>(x, part, S, k, d, g, o, eps);
 }
 
 bool residual_rmsnorm_ok(int d) { return d > 0 && (d <= 4096 ? d % 256 == 0 : d <= 8192 && d % 512 == 0); }

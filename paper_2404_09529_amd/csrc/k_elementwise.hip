@@ -183,7 +183,7 @@ struct TableArgs {
     // indices are written beside it (see decode_start); null for a table of positions 0, 1, ..
     const int32_t *pos0, *gen_off;
     int step;
-    int32_t *slot_pos, *slot_kv, *ident;
+    int32_t *slot_pos, *slot_kv;
 };
 
 template <typename TE, int NC>
@@ -202,8 +202,6 @@ __global__ __launch_bounds__(kBlock) void start_kernel(float* __restrict__ x, co
             const int m = static_cast<int>(p);
             ta.slot_pos[m] = m;                          // row m of this step's table
             ta.slot_kv[m] = ta.gen_off[m] + ta.step;     // the row this step appends to
-            ta.ident[m] = m;
-            if ((p + 1) * ta.half == ta.n) ta.ident[m + 1] = m + 1;
         }
         return;
     }
@@ -341,7 +339,7 @@ void prefill_start(int dtype, float2* table, int P, int D, float theta, float* x
                    const int32_t* tokens, const int32_t* slot_kv, int T, int d, const float* g, void* xn, float eps,
                    hipStream_t s) {
     const TableArgs ta{table, int64_t(P) * (D / 2), D / 2, D, static_cast<double>(theta), nullptr, nullptr, 0,
-                       nullptr, nullptr, nullptr};
+                       nullptr, nullptr};
     if (dtype == PP_BF16)
         start_dispatch(x, static_cast<const bf16*>(E), tokens, slot_kv, T, d, vocab, g, at<bf16>(xn), eps, ta, s);
     else
@@ -349,10 +347,10 @@ void prefill_start(int dtype, float2* table, int P, int D, float theta, float* x
 }
 
 void decode_start(int dtype, const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
-                  int32_t* slot_kv, int32_t* ident, float* x, const void* E, int vocab, const int32_t* tokens, int d,
+                  int32_t* slot_kv, float* x, const void* E, int vocab, const int32_t* tokens, int d,
                   const float* g, void* xn, float eps, hipStream_t s) {
     const TableArgs ta{table, int64_t(Ly.k) * (D / 2), D / 2, D, static_cast<double>(theta), Ly.pos0, Ly.gen_off, step,
-                       slot_pos, slot_kv, ident};
+                       slot_pos, slot_kv};
     if (dtype == PP_BF16)
         start_dispatch(x, static_cast<const bf16*>(E), tokens, nullptr, Ly.k, d, vocab, g, at<bf16>(xn), eps, ta, s);
     else

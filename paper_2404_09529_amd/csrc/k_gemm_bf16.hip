@@ -523,11 +523,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
 
 namespace ppk {
 
-namespace {
-
-constexpr size_t kLds = LDS_BYTES;
-
-int cu_count() {   // a multiple of 8, so that every XCD runs the same number of workgroups
+int cu_count() {
     static const int n = [] {
         int dev = 0, v = 0;
         (void)hipGetDevice(&dev);
@@ -536,6 +532,10 @@ int cu_count() {   // a multiple of 8, so that every XCD runs the same number of
     }();
     return n;
 }
+
+namespace {
+
+constexpr size_t kLds = LDS_BYTES;
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

@@ -79,6 +79,16 @@ __device__ __forceinline__ int b_row(int r) {
     }
 }
 
+// Where a kernel's results go beside C.
+template <int EPI>
+struct OutOf {
+    using type = ppk::QkvOut;
+};
+template <>
+struct OutOf<ppk::kLogits> {
+    using type = LogitsOut;
+};
+
 // mt_first: index of the first entry of the row-tile list (or of the 256-row tiles of M) that
 // this launch takes; n_mt entries from there.  Each is kListRows / BM row tiles; those of the
 // batch's last entry that start past M are left out.  The (row tile, column tile) list goes
@@ -90,7 +100,7 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
                                                              const bf16* __restrict__ B, int64_t ldb,
                                                              void* __restrict__ Cv, int64_t ldc, int M, int N, int K,
                                                              const int32_t* __restrict__ mtile_m0, int mt_first,
-                                                             int n_mt, ppk::QkvOut qo) {
+                                                             int n_mt, typename OutOf<EPI>::type qo) {
     using G = Geom<BM, BN, NS>;
     constexpr int MB = G::MB, NB = G::NB;
     constexpr int SUB = kListRows / BM, GM = 2048 / BM;
@@ -100,7 +110,7 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
 
     const int last0 = mtile_m0 ? mtile_m0[mt_first + n_mt - 1] : (mt_first + n_mt - 1) * kListRows;
     const int tiles_m = (n_mt - 1) * SUB + min(SUB, (M - last0 + BM - 1) / BM);
-    const int tiles_n = N / BN;
+    const int tiles_n = EPI == ppk::kLogits ? (N + BN - 1) / BN : N / BN;   // (only the logits' N may be ragged)
     const int xcd = blockIdx.x & 7, slot0 = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
     const int total = tiles_m * tiles_n, per = (total + 7) / 8;
     const int g_begin = xcd * per, n_local = min(per, total - g_begin);
@@ -144,8 +154,16 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
             constexpr int b_rows = EPI == ppk::kQkvRope && BN == 64 ? 96 : BN;
             rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(A + int64_t(m0) * lda), 0,
                                                        static_cast<int>(a_rows * lda2), kRsrcWord3);
+            const int b_here = EPI == ppk::kLogits ? min(N - n0, b_rows) : b_rows;
             rsrc_b = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(B + int64_t(n0) * ldb), 0,
-                                                       static_cast<int>(b_rows * ldb2), kRsrcWord3);
+                                                       static_cast<int>(b_here * ldb2), kRsrcWord3);
+            if constexpr (EPI == ppk::kLogits) {   // rows past the vocabulary read its last row
+#pragma unroll
+                for (int t = 0; t < G::B_LD; ++t) {
+                    const int r = 8 * (G::B_LD * wave + t) + lrow;
+                    voff_b[t] = static_cast<int>(min(r, b_here - 1) * ldb2) + 16 * ((lane & 7) ^ swz(r));
+                }
+            }
 #pragma unroll
             for (int t = 0; t < G::A_LD; ++t) {
                 const int r = 8 * (G::A_LD * wave + t) + lrow;
@@ -244,7 +262,10 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
         }
         int m0, n0;
         tile_m0n0(c_local, m0, n0);
-        epilogue_direct<EPI, NB, MB>(acc, Cv, ldc, M, m0 + wm * 16 * MB, n0, wn, lane, qo);
+        if constexpr (EPI == ppk::kLogits)
+            epilogue_logits<MB>(acc, M, m0 + wm * 16 * MB, n0 + wn * 16 * NB, lane, qo);
+        else
+            epilogue_direct<EPI, NB, MB>(acc, Cv, ldc, M, m0 + wm * 16 * MB, n0, wn, lane, qo);
         c_local += n_slots;
         if (c_local >= n_local) break;
     }
@@ -253,7 +274,8 @@ __global__ __launch_bounds__(NT, WGS) void gemm_tiles_kernel(const bf16* __restr
 
 // TILE: index into kTileRows / kTileCols; NS ring slots, WGS workgroups per CU.
 template <int EPI, int TILE, int NS, int WGS>
-void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits) {
+void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits,
+            const typename OutOf<EPI>::type& out) {
     constexpr int BM = ppk::kTileRows[TILE], BN = ppk::kTileCols[TILE];
     using G = Geom<BM, BN, NS>;
     static_assert(WGS * G::LDS <= 160 * 1024, "LDS of a CU's workgroups");
@@ -263,21 +285,21 @@ void launch(const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_
         return true;
     }();
     (void)attr;
-    const int64_t tiles = int64_t(n_mt) * (kListRows / BM) * (g.N / BN);   // at least the kernel's count
+    const int64_t tiles = int64_t(n_mt) * (kListRows / BM) * ((g.N + BN - 1) / BN);   // at least the kernel's count
     const int64_t grid = 8 * std::min<int64_t>((tiles + 7) / 8, WGS * (n_cu / 8));
     gemm_tiles_kernel<EPI, BM, BN, NS, WGS><<<dim3(static_cast<unsigned>(grid), splits), NT, G::LDS, s>>>(
         static_cast<const bf16*>(g.A), g.lda, static_cast<const bf16*>(g.B), g.ldb, g.C, g.ldc, g.M, g.N, g.K, g.mtile_m0,
-        mt_first, n_mt, g.qkv);
+        mt_first, n_mt, out);
 }
 
 template <int EPI>
 void launch_tile(int tile, const ppk::GemmArgs& g, int mt_first, int n_mt, int n_cu, hipStream_t s, int splits) {
     switch (tile) {
-        case 0: return launch<EPI, 0, 6, 2>(g, mt_first, n_mt, n_cu, s, splits);
-        case 1: return launch<EPI, 1, 5, 2>(g, mt_first, n_mt, n_cu, s, splits);
-        case 2: return launch<EPI, 2, 3, 2>(g, mt_first, n_mt, n_cu, s, splits);
-        case 3: return launch<EPI, 3, 5, 1>(g, mt_first, n_mt, n_cu, s, splits);
-        default: return launch<EPI, 4, 3, 1>(g, mt_first, n_mt, n_cu, s, splits);
+        case 0: return launch<EPI, 0, 6, 2>(g, mt_first, n_mt, n_cu, s, splits, g.qkv);
+        case 1: return launch<EPI, 1, 5, 2>(g, mt_first, n_mt, n_cu, s, splits, g.qkv);
+        case 2: return launch<EPI, 2, 3, 2>(g, mt_first, n_mt, n_cu, s, splits, g.qkv);
+        case 3: return launch<EPI, 3, 5, 1>(g, mt_first, n_mt, n_cu, s, splits, g.qkv);
+        default: return launch<EPI, 4, 3, 1>(g, mt_first, n_mt, n_cu, s, splits, g.qkv);
     }
 }
 
@@ -293,6 +315,14 @@ void gemm_tiles(int epi, int tile, const GemmArgs& g, int mt_first, int n_mt, in
         case kPartial: return launch_tile<kPartial>(tile, g, mt_first, n_mt, n_cu, s, splits);
         default: return launch_tile<kQkvRope>(tile, g, mt_first, n_mt, n_cu, s, splits);
     }
+}
+
+void lm_head_tiles(const void* hl, int k, const void* W, int V, int d, float* logits, void* part, int n_blocks,
+                   hipStream_t s) {
+    const LogitsOut out{logits, static_cast<ArgMax*>(part), V, n_blocks,
+                        V % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0};
+    launch<kLogits, 4, 3, 1>(GemmArgs{hl, d, W, d, nullptr, 0, k, V, d, nullptr, QkvOut{}}, 0, (k + kListRows - 1) / kListRows,
+                             cu_count(), s, 1, out);
 }
 
 }  // namespace ppk

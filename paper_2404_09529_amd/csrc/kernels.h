@@ -36,7 +36,7 @@ void kv_scatter(int dtype, const void* qkv, int64_t ld, int k_col, int kvw, void
                 const int32_t* slot_kv, int T, hipStream_t s);
 
 // Epilogues of the projection GEMMs C = A B^T (A [M, K] activations, B [N, K] weights).
-enum Epilogue { kStore = 0, kResidual = 1, kSwiGLU = 2, kQkvRope = 3, kPartial = 4 };
+enum Epilogue { kStore = 0, kResidual = 1, kSwiGLU = 2, kQkvRope = 3, kPartial = 4, kLogits = 5 };
 
 // Destinations of the kQkvRope epilogue.  B is the stacked [Wq; Wk; Wv] (bf16: head dim 128);
 // q [M, ldq] receives the rotated queries, kc / vc [*, ldkv] the rotated keys and the values
@@ -106,6 +106,10 @@ void attention_f32(const float* q, int64_t ldq, const float* kc, const float* vc
 size_t first_token_workspace(int dtype, int k, int V, int d);
 void first_token(int dtype, const float* hidden, const int32_t* prompt_kv_off, int k, const void* lm_head, int V,
                  int d, void* workspace, float* logits, int32_t* tokens, hipStream_t s);
+// The same for the rows already in dtype at the start of the workspace ([k, d]; room for k rounded up
+// to 16, whose other rows may hold anything).
+void next_token(int dtype, int k, const void* lm_head, int V, int d, void* workspace, float* logits, int32_t* tokens,
+                hipStream_t s);
 // The current GPU's copy of the static PP_FIRST_TOKEN_SCRATCH_BYTES workspace of
 // pp_first_token_noalloc (its address looked up once per device).
 hipError_t first_token_scratch(void** ptr);
@@ -124,10 +128,10 @@ struct DecodeLayout {
 
 // The first launch of a decode step.  Per prompt i < k: table[i] = cos/sin((pos0[i] + step)
 // theta^(-2j/D)) for j < D/2 (float64, float2 [k][D/2]); slot_pos[i] = i; slot_kv[i] = gen_off[i] +
-// step; ident[i] = i for i <= k (k + 1 entries); x[i] = E[tokens[i]] (float32; 0 for an id not in
+// step; x[i] = E[tokens[i]] (float32; 0 for an id not in
 // [0, vocab)) and xn[i] = RMSNorm(x[i]) * g in dtype.
 void decode_start(int dtype, const DecodeLayout& Ly, int step, int D, float theta, float2* table, int32_t* slot_pos,
-                  int32_t* slot_kv, int32_t* ident, float* x, const void* E, int vocab, const int32_t* tokens, int d,
+                  int32_t* slot_kv, float* x, const void* E, int vocab, const int32_t* tokens, int d,
                   const float* g, void* xn, float eps, hipStream_t s);
 
 // The decode attention's per-chunk results (k x H x n_chunks x (D + 4) float32: o[D], max,
@@ -173,9 +177,9 @@ void decode_gemm_o(int k, const AttnChunks& ac, const void* W, int64_t ldw, int 
                    hipStream_t s);
 
 // x[m] += sum of the S splits of part (split order; S = 0: nothing), stored back, then
-// out[m] = RMSNorm(x[m]) * g in dtype_out (PP_BF16 or PP_F32); k rows of d <= 4096.
-void residual_rmsnorm(int dtype_out, float* x, const float* part, int S, int k, int d, const float* g, void* out,
-                      float eps, hipStream_t s);
+// out[m] = RMSNorm(x[m]) * g in bf16; k rows.
+void residual_rmsnorm(float* x, const float* part, int S, int k, int d, const float* g, void* out, float eps,
+                      hipStream_t s);
 // Widths residual_rmsnorm takes: d % 256 == 0 up to 4096, d % 512 == 0 up to 8192.
 bool residual_rmsnorm_ok(int d);
 

@@ -127,6 +127,30 @@ def test_first_token_ties_go_to_the_lowest_id_and_nan_gives_minus_one(d):
     assert tokens[1] == ref_tok[1] or ref[1, tokens[1]] >= ref[1].max() - 1e-3
 
 
+@pytest.mark.parametrize("k,V,d", [(65, 2, 256), (128, 127, 256), (129, 257, 512), (70, 385, 2048), (257, 1003, 256),
+                                   (66, 65537, 256)])
+def test_first_token_bf16_tiles(k, V, d):
+    """More than 64 prompts: vocabularies around the 128- and 256-row blocks of a tile, odd ones,
+    prompt counts around its 128 rows; ties and an all-NaN row; with and without logits."""
+    rng = np.random.default_rng([k, V, d])
+    lengths = list(rng.integers(1, 4, k))
+    hidden = rng.standard_normal((int(np.sum(lengths)), d)).astype(np.float32)
+    lm_head = rand_bf16(rng, (V, d), 0.02)
+    ends = np.cumsum(lengths) - 1
+    ids = sorted(set(int(v) for v in (V // 3, V // 2, V - 1)))
+    planted = D.round_bf16(0.05 * D.round_bf16(hidden[ends[k - 2]].astype(np.float64)))
+    for v in ids:
+        lm_head[v] = planted
+    keep = hidden.copy()
+    hidden[ends[k - 1]] = np.nan
+    tokens, logits = _run(lengths, hidden, lm_head)
+    assert tokens[k - 2] == ids[0] and tokens[k - 1] == -1
+    assert np.all(np.isnan(logits[k - 1]))
+    assert np.array_equal(_run(lengths, hidden, lm_head, want_logits=False)[0], tokens)
+    n = int(ends[k - 2]) + 1
+    _check(lengths[:-1], keep[:n], lm_head, tokens[:-1], logits[:-1])
+
+
 def test_first_token_f32():
     rng = np.random.default_rng(13)
     lengths = [6, 1, 11, 4]
