@@ -47,14 +47,13 @@
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = 256, BN = 256, BK = 64;   // BM: rows of a full tile and of a row-tile list's entry
 constexpr int NT = 256;                  // 4 wavefronts, one per SIMD
 constexpr int ROW_B = BK * 2;            // LDS row: 128 bytes = 8 chunks of 16 bytes
 constexpr int SLOT_B = BM * ROW_B;       // one operand of one K-step (32 KB)
 constexpr int NSLOT = 5;                 // the whole 160 KB LDS of a CU
 constexpr int LDS_BYTES = NSLOT * SLOT_B;
-constexpr int LOADS = SLOT_B / 1024 / 4; // 1 KB loads per wavefront per operand tile (8)
-static_assert(LOADS == 8, "the vmcnt wait of the K loop counts 8 loads per operand tile");
+constexpr int LOADS = SLOT_B / 1024 / 4; // 1 KB loads per wavefront per weight tile (8)
 
 // s_waitcnt immediate: vmcnt(n) and lgkmcnt(0), expcnt not waited for (gfx9 encoding:
 // vmcnt bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
@@ -85,7 +84,8 @@ __device__ __forceinline__ void barrier() {
 // registers at this point: the epilogue then moves them to vector registers a pair of blocks
 // at a time instead of all at once (which would need every vector register and spill).  The
 // accumulators are dead afterwards.
-__device__ __forceinline__ void take_pair(f32x4 (&acc)[8][8], int jp, f32x4 (&c)[8][2]) {
+template <int MB>
+__device__ __forceinline__ void take_pair(f32x4 (&acc)[8][MB], int jp, f32x4 (&c)[8][2]) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -108,11 +108,52 @@ __device__ __forceinline__ void stage_put(char* stg, int r, int c, int half, bf1
 // (i, j) lane l holds activation row mb + 16 j + l % 16 and the 4 consecutive weight rows
 // nb0 + 16 i + 4 (l / 16) + 0..3.  stg is this wavefront's 8 KB of LDS, free for the duration
 // of the epilogue.
-template <int EPI>
-__device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ Cv, int64_t ldc, int M,
+template <int EPI, int MB>
+__device__ __forceinline__ void epilogue(f32x4 (&acc)[8][MB], void* __restrict__ Cv, int64_t ldc, int M,
                                          int mb, int nb0, int lane, const ppk::QkvOut& qo, char* stg) {
     const int lr = lane & 15, g = lane >> 4;
-    if constexpr (EPI == ppk::kResidual) {
+    if constexpr (EPI == ppk::kResidual && MB < 8) {
+        // As below in halves of 64 columns (4 KB: a shorter tile's wavefront has MB KB to stage in):
+        // instruction k covers rows 4 k .. 4 k + 3, 256 bytes each; staging row r's 16-byte chunk q
+        // sits at q ^ r.
+        float* C = static_cast<float*>(Cv);
+        f32x4 cbuf[2][4];
+        auto load_half = [&](int t, f32x4 (&buf)[4]) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int m = min(mb + 16 * (t >> 1) + 4 * k + g, M - 1);
+                buf[k] = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4*>(C + int64_t(m) * ldc + nb0 + 64 * (t & 1) + 4 * lr));
+            }
+        };
+        load_half(0, cbuf[0]);
+#pragma unroll
+        for (int t = 0; t < 2 * MB; ++t) {
+            if (t + 1 < 2 * MB) load_half(t + 1, cbuf[(t + 1) & 1]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                asm volatile("" : "+a"(acc[4 * (t & 1) + i][t >> 1]) : : "memory");
+                *reinterpret_cast<f32x4*>(stg + lr * 256 + (((4 * i + g) ^ lr) * 16)) = acc[4 * (t & 1) + i][t >> 1];
+            }
+            f32x4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int r = 4 * k + g;
+                v[k] = *reinterpret_cast<const f32x4*>(stg + r * 256 + ((lr ^ r) * 16));
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int m = mb + 16 * (t >> 1) + 4 * k + g;
+                if (m < M)
+                    __builtin_nontemporal_store(
+                        v[k] + cbuf[t & 1][k],
+                        reinterpret_cast<f32x4*>(C + int64_t(m) * ldc + nb0 + 64 * (t & 1) + 4 * lr));
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+        return;
+    }
+    if constexpr (EPI == ppk::kResidual && MB == 8) {
         // C[m][nb0 ..] += this lane's accumulators, one 16-row block j at a time, staged
         // through LDS (16 rows x 128 floats, 512-byte rows) so that C is read and written as
         // whole rows: instruction k covers rows 2 k and 2 k + 1, 16 bytes per lane.  C moves
@@ -177,9 +218,9 @@ __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ 
         // are requested before block j is stored (vmcnt counts stores and completes in order).
         const int head = nb0 >> 7;
         const int kind = head < qo.H ? 0 : (head < qo.H + qo.Hkv ? 1 : 2);   // q, k, v (uniform)
-        int drow[8], pos[8];
+        int drow[MB], pos[MB];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < MB; ++j) {
             const int m = mb + 16 * j + lr, mc = min(m, M - 1);
             const int kv = kind > 0 ? qo.slot_kv[mc] : m;
             drow[j] = m < M ? kv : -1;
@@ -200,8 +241,8 @@ __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ 
                                      (head - qo.H - (kind == 2 ? qo.Hkv : 0)) * 128;
         const int64_t ld = kind == 0 ? qo.ldq : qo.ldkv;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (kind < 2 && j + 1 < 8) load_tab(j + 1, tb[(j + 1) & 1]);
+        for (int j = 0; j < MB; ++j) {
+            if (kind < 2 && j + 1 < MB) load_tab(j + 1, tb[(j + 1) & 1]);
             f32x4 c[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -252,7 +293,7 @@ __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ 
     // bf16 outputs: 128 columns (16 chunks) per row, or 64 (8 chunks) after SwiGLU
     constexpr int CH = EPI == ppk::kSwiGLU ? 8 : 16;
 #pragma unroll
-    for (int jp = 0; jp < 4; ++jp) {
+    for (int jp = 0; jp < MB / 2; ++jp) {
         f32x4 c[8][2];
         take_pair(acc, jp, c);
 #pragma unroll
@@ -299,12 +340,16 @@ __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][8], void* __restrict__ 
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
 }
 
-template <int EPI>
+// MB: 16-row activation blocks of a wavefront, so 32 MB rows of a tile (8: 256; 6: 192, without a
+// row-tile list).
+template <int EPI, int MB>
 __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict__ A, int64_t lda,
                                                           const bf16* __restrict__ B, int64_t ldb,
                                                           void* __restrict__ Cv, int64_t ldc, int M, int K,
                                                           const int32_t* __restrict__ mtile_m0, int tiles_m,
                                                           int tiles_n, int balanced, ppk::QkvOut qo) {
+    constexpr int TM = 32 * MB, GM = 64 / MB;   // rows of a tile; M-tiles of a group
+    static_assert(MB == 8 || (MB == 6 && EPI != ppk::kStore), "a wavefront stages up to MB KB of its results");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: LDS bases and descriptors in SGPRs
@@ -341,13 +386,13 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
         n_local = m_cnt * tiles_n;
     }
     if (m_cnt <= 0 || n_local <= 0) return;
-    const int n_groups = (m_cnt + 7) / 8, gm = (m_cnt + n_groups - 1) / n_groups;
+    const int n_groups = (m_cnt + GM - 1) / GM, gm = (m_cnt + n_groups - 1) / n_groups;
     auto tile_m0 = [&](int local) {
         const int gi = g_begin + local;
         const int group = gi / (gm * tiles_n), within = gi - group * gm * tiles_n;
         const int first = group * gm, gsz = min(m_cnt - first, gm);
         const int mt = m_begin + first + within % gsz;
-        return mtile_m0 ? mtile_m0[mt] : mt * BM;
+        return mtile_m0 ? mtile_m0[mt] : mt * TM;
     };
     auto tile_n0 = [&](int local) {
         const int gi = g_begin + local;
@@ -364,10 +409,10 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
     // they were issued, and the results of the duplicated rows are never stored.
     const int64_t lda2 = lda * 2, ldb2 = ldb * 2;
     const int lrow = lane >> 3;
-    int chunk_off[LOADS], voff_b[LOADS], voff_a[LOADS];
+    int chunk_off[LOADS], voff_b[LOADS], voff_a[MB];
 #pragma unroll
     for (int t = 0; t < LOADS; ++t) {
-        chunk_off[t] = 16 * ((lane & 7) ^ swz(8 * (t & 1) + lrow));
+        chunk_off[t] = 16 * ((lane & 7) ^ swz(8 * (t & 1) + lrow));   // 8 MB wave is a multiple of 16: A's too
         voff_b[t] = static_cast<int>((64 * wave + 8 * t + lrow) * ldb2) + chunk_off[t];
     }
 
@@ -380,14 +425,14 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
     auto set_cursor_tile = [&]() {
         if (l_local < n_local) {
             const int m0 = tile_m0(l_local), n0 = tile_n0(l_local);
-            const int a_rows = min(M - m0, BM);
+            const int a_rows = min(M - m0, TM);
             rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(A + int64_t(m0) * lda), 0,
                                                        static_cast<int>(a_rows * lda2), kRsrcWord3);
             rsrc_b = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(B + int64_t(n0) * ldb), 0,
                                                        static_cast<int>(BN * ldb2), kRsrcWord3);
 #pragma unroll
-            for (int t = 0; t < LOADS; ++t)
-                voff_a[t] = static_cast<int>(min(64 * wave + 8 * t + lrow, a_rows - 1) * lda2) + chunk_off[t];
+            for (int t = 0; t < MB; ++t)
+                voff_a[t] = static_cast<int>(min(8 * (MB * wave + t) + lrow, a_rows - 1) * lda2) + chunk_off[t];
         } else {
             rsrc_a = rsrc_0;
             rsrc_b = rsrc_0;
@@ -395,8 +440,9 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
     };
     set_cursor_tile();
     auto load_a = [&](int t) {
-        char* dst = smem + l_sa * SLOT_B + (wave * LOADS + t) * 1024;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lds_void*)dst, 16, voff_a[t], l_kt * BK * 2, 0, 0);
+        char* dst = smem + l_sa * SLOT_B + (wave * MB + t) * 1024;
+        const int voff = voff_a[t];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lds_void*)dst, 16, voff, l_kt * BK * 2, 0, 0);
     };
     auto load_b = [&](int t) {
         char* dst = smem + l_sb * SLOT_B + (wave * LOADS + t) * 1024;
@@ -423,20 +469,20 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         const int phys = ((4 * ks + (lane >> 4)) ^ swz(lane & 15)) * 16;
-        a_lds[ks] = (wm * 128 + (lane & 15)) * ROW_B + phys;
+        a_lds[ks] = (wm * 16 * MB + (lane & 15)) * ROW_B + phys;
         b_lds[ks] = (wn * 128 + (lane & 15)) * ROW_B + phys;
     }
-    struct Frags { bf16x8 w[8], a[8]; };
+    struct Frags { bf16x8 w[8], a[MB]; };
     // fragment q of sub-step ks of the step held in slots (sa, sb), in the order the MFMAs
-    // first need them: w0, a0..a7, w1..w7
+    // first need them: w0, a0.., w1..w7
     auto read_one = [&](int sa, int sb, int ks, int q, Frags& f) {
         if (q == 0) {
             f.w[0] = *reinterpret_cast<const bf16x8*>(smem + sb * SLOT_B + b_lds[ks]);
-        } else if (q < 9) {
+        } else if (q <= MB) {
             const int j = q - 1;
             f.a[j] = *reinterpret_cast<const bf16x8*>(smem + sa * SLOT_B + a_lds[ks] + j * 16 * ROW_B);
         } else {
-            const int i = q - 8;
+            const int i = q - MB;
             f.w[i] = *reinterpret_cast<const bf16x8*>(smem + sb * SLOT_B + b_lds[ks] + i * 16 * ROW_B);
         }
     };
@@ -454,7 +500,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
-        for (int t = 0; t < LOADS; ++t) load_a(t);
+        for (int t = 0; t < MB; ++t) load_a(t);
 #pragma unroll
         for (int t = 0; t < LOADS; ++t) load_b(t);
         advance_cursor();
@@ -464,13 +510,13 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
     Frags F0, F1;
     int c_sa = 0, c_sb = 1;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) read_one(c_sa, c_sb, 0, q, F0);
+    for (int q = 0; q < 8 + MB; ++q) read_one(c_sa, c_sb, 0, q, F0);
     while (true) {
-        f32x4 acc[8][8];
+        f32x4 acc[8][MB];
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{};
+            for (int j = 0; j < MB; ++j) acc[i][j] = f32x4{};
         // One sub-step: the 64 MFMAs on `cur`, with the 16 fragment reads of the next sub-step
         // (into `nxt`) and one load after every eighth MFMA, in a fixed order: the reads and
         // loads issue while the matrix core works.  The first sub-step (A loads) ends at the
@@ -478,18 +524,20 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
         // by the time the barrier's wait checks them; the second spreads them over all 64.
         auto substep = [&](const Frags& cur, Frags& nxt, int rsa, int rsb, int rks, bool first) {
 #pragma unroll
-            for (int m = 0; m < 64; ++m) {
-                const int i = m >> 3, j = m & 7;
+            for (int m = 0; m < 8 * MB; ++m) {
+                const int i = m / MB, j = m % MB;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.w[i], cur.a[j], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
+                // read q after MFMA q span / (8 + MB)
+                const int span = first ? 6 * MB : 8 * MB;
+#pragma unroll
+                for (int q = (m * (8 + MB) + span - 1) / span;
+                     q < ((m + 1) * (8 + MB) + span - 1) / span && q < 8 + MB; ++q)
+                    read_one(rsa, rsb, rks, q, nxt);
                 if (first) {
-                    if (m % 3 == 0 && m < 48) read_one(rsa, rsb, rks, m / 3, nxt);
+                    if (m % 8 == 2) load_a(m / 8);
                 } else {
-                    if ((m & 3) == 0) read_one(rsa, rsb, rks, m >> 2, nxt);
-                }
-                if ((m & 7) == 2) {
-                    if (first) load_a(m >> 3);
-                    else load_b(m >> 3);
+                    if (m % MB == 2) load_b(m / MB);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -498,7 +546,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
             const int n_sa = c_sa >= NSLOT - 2 ? c_sa + 2 - NSLOT : c_sa + 2;
             const int n_sb = c_sb >= NSLOT - 2 ? c_sb + 2 - NSLOT : c_sb + 2;
             substep(F0, F1, c_sa, c_sb, 1, true);    // A tile of g+2
-            if (l_local < n_local) __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(LOADS));
+            if (l_local < n_local) __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(MB));
             else __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
             barrier();
             substep(F1, F0, n_sa, n_sb, 0, false);   // B tile of g+2
@@ -511,8 +559,8 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(const bf16* __restrict
         // exactly the part of it that w's own loads refill.
         const int m0 = tile_m0(c_local), n0 = tile_n0(c_local);
         const int free_slot = c_sb >= 2 ? c_sb - 2 : c_sb + NSLOT - 2;
-        epilogue<EPI>(acc, Cv, ldc, M, m0 + wm * 128, n0 + wn * 128, lane, qo,
-                      smem + free_slot * SLOT_B + wave * LOADS * 1024);
+        epilogue<EPI, MB>(acc, Cv, ldc, M, m0 + wm * 16 * MB, n0 + wn * 128, lane, qo,
+                          smem + free_slot * SLOT_B + wave * MB * 1024);
         c_local += n_slots;
         if (c_local >= n_local) break;
     }
@@ -551,11 +599,11 @@ XcdSplit xcd_split(int tiles_m, int tiles_n, int wg_per_xcd) {
     return XcdSplit{balanced, balanced ? even : blocked};
 }
 
-// The first n_mt 256-row tiles on the 256 x 256 kernel.
-template <int EPI>
+// The first n_mt tiles of 32 MB rows on this kernel.
+template <int EPI, int MB>
 void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
     static bool attr = [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, MB>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         return true;
     }();
@@ -563,9 +611,10 @@ void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
     // one workgroup per CU (each needs the whole 160 KB LDS); never more workgroups than tiles
     const int tiles_n = g.N / BN, wg_per_xcd = cu_count() / 8;
     const XcdSplit x = xcd_split(n_mt, tiles_n, wg_per_xcd);
-    const int M = g.mtile_m0 ? g.M : min(g.M, n_mt * BM);
-    gemm_bf16_kernel<EPI><<<8 * min(wg_per_xcd, x.tiles), NT, kLds, s>>>(
-        static_cast<const bf16*>(g.A), g.lda, static_cast<const bf16*>(g.B), g.ldb, g.C, g.ldc, M, g.K, g.mtile_m0, n_mt,
+    const int M = MB == 8 && !g.mtile_m0 ? min(g.M, n_mt * BM) : g.M;
+    gemm_bf16_kernel<EPI, MB><<<8 * min(wg_per_xcd, x.tiles), NT, kLds, s>>>(
+        static_cast<const bf16*>(g.A), g.lda, static_cast<const bf16*>(g.B), g.ldb, g.C, g.ldc, M, g.K,
+        MB == 8 ? g.mtile_m0 : nullptr, n_mt,
         tiles_n, x.balanced, g.qkv);
 }
 
@@ -580,13 +629,15 @@ void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
 // round: the rows past the whole rounds then go to smaller tiles (2926 rows, N = 6144, K = 4096:
 // 288 tiles, two rounds, 191 us; 240 on one round and 366 rows as 128 x 128 tiles, 142 us).  A
 // split must promise 5%: past about 20 rounds the CUs no longer run in rounds, and a predicted
-// 2% (27,721 rows, N = 12288) measured as nothing.
-constexpr float kBigStep = 1.34f, kLaunch = 4.0f;
+// 2% (27,721 rows, N = 12288) measured as nothing.  Rows that make three quarters of a round make a
+// whole one of 192-row tiles at 1.10 us a step (2926 rows, N = 4096: 192 tiles of 256 rows, O 107 and
+// down 320 us; 256 of 192 rows, 90 and 274 us).
+constexpr float kBigStep = 1.34f, kStep192 = 1.10f, kLaunch = 4.0f;
 
 struct GemmSplit {
-    int big, tile;
+    int big, tile;   // big < 0: every row on 192-row tiles
 };
-GemmSplit gemm_split(int n_mt, int M, int N, int K, bool list) {
+GemmSplit gemm_split(int epi, int n_mt, int M, int N, int K, bool list) {
     const int tiles_n = N / BN, wg = cu_count() / 8;
     const float steps = static_cast<float>(K / BK);
     auto big_time = [&](int n) {
@@ -613,6 +664,11 @@ GemmSplit gemm_split(int n_mt, int M, int N, int K, bool list) {
     for (int r = rounds; r > 0 && r >= rounds - 1; --r) {
         const int big = r * 8 * wg / tiles_n;
         if (big > 0 && big < n_mt) consider(big);
+    }
+    // 192-row tiles (the list, if any, must name every tile: it counts in 256 rows)
+    if (epi != kStore && n_mt == ceil_div(M, BM)) {
+        const float time = kLaunch + steps * kStep192 * ceil_div(xcd_split(ceil_div(M, 192), tiles_n, wg).tiles, wg);
+        if (time < best_time * 0.95f) best = GemmSplit{-1, 0};
     }
     return best;
 }
@@ -646,8 +702,11 @@ template <int EPI>
 void gemm(const GemmArgs& g, int n_mtiles, hipStream_t s) {
     const int n_mt = g.mtile_m0 ? n_mtiles : ceil_div(g.M, BM);
     if (n_mt <= 0) return;
-    const GemmSplit sp = gemm_split(n_mt, g.M, g.N, g.K, g.mtile_m0 != nullptr);
-    if (sp.big > 0) launch<EPI>(g, sp.big, s);
+    const GemmSplit sp = gemm_split(EPI, n_mt, g.M, g.N, g.K, g.mtile_m0 != nullptr);
+    if constexpr (EPI != kStore) {
+        if (sp.big < 0) return launch<EPI, 6>(g, ceil_div(g.M, 192), s);
+    }
+    if (sp.big > 0) launch<EPI, 8>(g, sp.big, s);
     if (sp.big < n_mt) gemm_tiles(EPI, sp.tile, g, sp.big, n_mt - sp.big, cu_count(), s);
 }
 

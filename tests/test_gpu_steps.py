@@ -103,11 +103,11 @@ def test_gemm_bf16_plan_row_tiles(epi):
         assert np.array_equal(got[~covered], base[~covered].astype(np.float64))
 
 
-# (M, N, K): every tile size of the projection GEMMs and the split of a batch between two of
-# them, with one row, tile edges + 1, fewer K-steps than the load ring holds (K = 64, 192) and an
+# (M, N, K): every tile size of the projection GEMMs (192-row tiles last) and the split of a batch
+# between two of them, with one row, tile edges + 1, fewer K-steps than the load ring holds (K = 64, 192) and an
 # odd number of them
 TILE_CASES = [(1, 256, 64), (33, 2048, 192), (65, 2048, 5504), (150, 6144, 2048), (344, 2048, 5504), (129, 512, 4160),
-              (344, 11008, 2048), (513, 4096, 14336), (700, 22016, 1024), (2926, 6144, 256), (1309, 11008, 128)]
+              (344, 11008, 2048), (513, 4096, 14336), (700, 22016, 1024), (2926, 6144, 256), (1309, 11008, 128), (2926, 4096, 320), (2881, 4096, 64)]
 
 
 @pytest.mark.parametrize("M,N,K", TILE_CASES)
@@ -148,7 +148,7 @@ def test_gemm_bf16_tiles(M, N, K, epi):
 
 
 @pytest.mark.parametrize("lengths,H,Hkv,d", [([1], 2, 0, 256), ([40, 7], 16, 16, 2048), ([172, 145], 16, 16, 2048),
-                                             ([301, 300, 77], 32, 8, 4096), ([418] * 7, 32, 8, 4096)])
+                                             ([301, 300, 77], 32, 8, 4096), ([418] * 7, 32, 8, 4096), ([418] * 7, 16, 8, 512)])
 def test_qkv_projection_tiles(lengths, H, Hkv, d):
     """The fused QKV projection on each tile size: bit for bit what the same prompts get inside a
     batch of large tiles."""
