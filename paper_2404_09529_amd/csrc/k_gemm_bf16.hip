@@ -675,7 +675,13 @@ GemmSplit gemm_split(int epi, int n_mt, int M, int N, int K, bool list) {
 
 // kPartial's tile and K splits for M rows of a decode step: the same estimate, with enough splits
 // to give the CUs something to do (N = d leaves 64 tiles of 64 x 64 at d 4096) against 8 bytes per
-// partial sum, written here and read by the norm, at about 4 TB/s.
+// partial sum, written here and read by the norm, at about 4 TB/s.  Rows that fit one tile of at most
+// 64 rows read each weight once, from HBM: one such workgroup alone on a CU then keeps too few
+// bytes in flight and takes kAlone times a step, so that a second one, of twice the splits, pays
+// (48 rows, N = 4096, K = 14336: 38 us in 4 splits, 28 in 8; a 48-prompt step of two layers 371 and
+// 348).  Several row tiles find the weights in L2: there more splits cost a step of 200 prompts 1%.
+constexpr float kAlone = 1.4f;
+
 struct PartialSplit {
     int tile, splits;
 };
@@ -687,8 +693,9 @@ PartialSplit partial_split(int M, int N, int K, int max_splits) {
         if (N % kTileCols[t]) continue;
         for (int s = 1; s <= max_splits && s <= 16 && s <= steps; ++s) {
             const int tiles = ceil_div(M, kTileRows[t]) * (N / kTileCols[t]) * s;
-            const float time = ceil_div(steps, s) * kTileStep[t] * ceil_div(ceil_div(tiles, 8), wg) +
-                               float(s) * M * N * 8e-6f / 4.f;
+            const int per_cu = ceil_div(ceil_div(tiles, 8), wg);
+            const float alone = per_cu == 1 && M <= kTileRows[t] && M <= 64 ? kAlone : 1.f;
+            const float time = ceil_div(steps, s) * kTileStep[t] * alone * per_cu + float(s) * M * N * 8e-6f / 4.f;
             if (time < best_time) {
                 best_time = time;
                 best = PartialSplit{t, s};
