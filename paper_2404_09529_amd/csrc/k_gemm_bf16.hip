@@ -675,12 +675,13 @@ GemmSplit gemm_split(int epi, int n_mt, int M, int N, int K, bool list) {
 
 // kPartial's tile and K splits for M rows of a decode step: the same estimate, with enough splits
 // to give the CUs something to do (N = d leaves 64 tiles of 64 x 64 at d 4096) against 8 bytes per
-// partial sum, written here and read by the norm, at about 4 TB/s.  Rows that fit one tile of at most
-// 64 rows read each weight once, from HBM: one such workgroup alone on a CU then keeps too few
-// bytes in flight and takes kAlone times a step, so that a second one, of twice the splits, pays
-// (48 rows, N = 4096, K = 14336: 38 us in 4 splits, 28 in 8; a 48-prompt step of two layers 371 and
-// 348).  Several row tiles find the weights in L2: there more splits cost a step of 200 prompts 1%.
-constexpr float kAlone = 1.4f;
+// partial sum, written here and read by the norm, at about 4 TB/s.  Up to 64 rows
+// each weight is read for one or two row tiles only, from HBM: a workgroup alone on its CU then
+// keeps too few bytes in flight and takes kAlone times a step, so that a second one, of twice the
+// splits, pays (48 rows, N = 4096, K = 14336: 38 us in 4 splits, 28 in 8; a 48-prompt step of two
+// layers 371 and 344; kAlone = 1.4 leaves O at fewer splits, 348).  More rows find the weights in
+// L2: there more splits cost a step of 200 prompts 1%.
+constexpr float kAlone = 1.6f;
 
 struct PartialSplit {
     int tile, splits;
@@ -694,7 +695,7 @@ PartialSplit partial_split(int M, int N, int K, int max_splits) {
         for (int s = 1; s <= max_splits && s <= 16 && s <= steps; ++s) {
             const int tiles = ceil_div(M, kTileRows[t]) * (N / kTileCols[t]) * s;
             const int per_cu = ceil_div(ceil_div(tiles, 8), wg);
-            const float alone = per_cu == 1 && M <= kTileRows[t] && M <= 64 ? kAlone : 1.f;
+            const float alone = per_cu == 1 && M <= 64 ? kAlone : 1.f;
             const float time = ceil_div(steps, s) * kTileStep[t] * alone * per_cu + float(s) * M * N * 8e-6f / 4.f;
             if (time < best_time) {
                 best_time = time;
