@@ -227,8 +227,8 @@ pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const pp_dplan* 
                      float* hidden, void* k_cache, void* v_cache, void* stream);
 
 /* ------------------------------------------------------------------------------------------
- * Single steps of pp_prefill.  Each enqueues exactly the kernel pp_prefill uses for that
- * step, on caller device buffers, for callers that assemble their own layer loop and for
+ * Single steps of pp_prefill.  Each computes the values of that step of pp_prefill (which
+ * joins some of them in one launch) on caller device buffers, for callers that assemble their own layer loop and for
  * step-by-step verification.  Same conventions: validated before enqueuing, asynchronous.
  * `rows` buffers are row-major with the stated row length; `plan` is a device plan.
  * ---------------------------------------------------------------------------------------- */
@@ -259,7 +259,7 @@ pp_status pp_gemm(int32_t dtype, int32_t epilogue, const void* A, int64_t lda, c
                   void* C, int64_t ldc, int32_t M, int32_t N, int32_t K, const pp_dplan* plan, void* stream);
 
 /* QKV projection with RESTART-PE and the KV-cache UNPACK fused into its epilogue (bf16 only;
- * the float32 path uses pp_gemm + pp_rope + pp_kv_scatter): [q | k | v] = xn wqkv^T with
+ * in float32 pp_gemm + pp_rope + pp_kv_scatter are these steps): [q | k | v] = xn wqkv^T with
  * float32 accumulation; q and k rotated (rotate-half RoPE) at each slot's restart position;
  * q stored to q_out [n_rows*capacity, H D]; k and v stored straight into the layer's caches
  * k_cache, v_cache [total_len, Hkv D] at row slot_kv[t] for every real slot t.

@@ -98,7 +98,7 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
 // weights are no longer nearly all that a projection reads: the streaming kernels' wavefronts each
 // fetch every prompt's row, and O's workgroups each merge every prompt's attention chunks.  At 48
 // prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O, gate/up, down)
-// against 19 / 5 + 14 / 52 / 28 for the tiles (O with
+// against 19 / 5 + 12 / 52 / 28 for the tiles (O with
 // its chunk merge as a kernel of its own).
 enum Mode { kStream, kTiles, kWhole };
 struct Plan {
