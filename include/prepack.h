@@ -418,7 +418,8 @@ pp_status pp_decode_workspace_size(const pp_config* cfg, const pp_gen_dlayout* l
  *
  * Numerics as pp_prefill (bf16 storage of weights, activations, q/k/v and caches; float32
  * accumulation, softmax and residual stream), and as pp_first_token for the choice.  The
- * packed and the full-batching layouts give bit-identical results.  Asynchronous; validated
+ * packed and the full-batching layouts give bit-identical results, and for a given k a prompt's
+ * results depend neither on n_new nor on the other prompts.  Asynchronous; validated
  * before enqueuing; the layout's device arrays are trusted to be what pp_gen_layout_make
  * wrote.
  * Errors: PP_ERR_INVALID_ARG (NULL pointer, step outside [0, n_new), inconsistent layout,

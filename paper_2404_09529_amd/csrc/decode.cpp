@@ -51,6 +51,29 @@ void projections(const pp_config* c, Proj (&p)[4]) {
 // bf16 widths whose O and down projections may leave partial sums to the residual norm.
 bool split_width(const pp_config* c) { return c->dtype == PP_BF16 && ppk::residual_rmsnorm_ok(c->d_model); }
 
+// How a step's projections run:
+//   kStream  up to 16 prompts at the widths they take: the weight-streaming kernels of k_decode.hip
+//   kTiles   up to 256: the prefill's GEMM tiles, O and down in up to tile_splits(k) K splits
+//   kWhole   the prefill's GEMMs as they are
+// The first two leave O's and down's partial sums to the norm that follows.  From 17 prompts on the
+// weights are no longer nearly all that a projection reads: the streaming kernels' wavefronts each
+// fetch every prompt's row, and O's workgroups each merge every prompt's attention chunks.  At 48
+// prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O, gate/up, down)
+// against 19 / 5 + 12 / 52 / 28 for the tiles (O with
+// its chunk merge as a kernel of its own).
+enum Mode { kStream, kTiles, kWhole };
+constexpr int kSplitPrompts = 256;
+Mode mode_of(const pp_config* c, const pp_gen_dlayout* g) {
+    if (!split_width(c) || g->k > kSplitPrompts) return kWhole;
+    return ppk::decode_stream_ok(g->k, c->d_model, c->n_heads * c->head_dim, c->ffn_dim) ? kStream : kTiles;
+}
+
+// The K splits that the tiles may take for O and down: 16 up to 128 prompts, fewer for more (2048 rows
+// of partial sums in all; few shapes would take more).  A function of k alone, so
+// that a prompt's results depend neither on the room reserved for generated tokens nor on the
+// lengths of the other prompts.
+int tile_splits(int k) { return std::min(16, 2048 / k); }
+
 int chunks(int n) { return (n + ppk::kDecodeChunk - 1) / ppk::kDecodeChunk; }
 
 Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
@@ -71,49 +94,25 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.attn = take(k * hd * e);
     L.act = take(k * F * e);
     L.h = take(k * d * 4);   // no longer used; the documented size of a workspace holds it
-    L.part = take(k * size_t(c->n_heads) * nch * (D + 4) * 4);
+    const size_t chunk_bytes = k * size_t(c->n_heads) * nch * (D + 4) * 4;
+    const Mode mode = mode_of(c, g);
+    if (mode == kTiles) {   // the chunk results are merged before O leaves its first partial sum
+        L.part = L.gpart = take(std::max(chunk_bytes, size_t(tile_splits(g->k)) * k * d * 4));
+    } else {
+        L.part = take(chunk_bytes);
+    }
+    if (mode == kStream) {  // O merges them while it leaves its partial sums
+        Proj p[4];
+        projections(c, p);
+        const int splits = std::max(ppk::skinny_split(p[1].N, p[1].K).splits,
+                                    ppk::decode_gemm_splits(g->k, p[3].N, p[3].K));
+        L.gpart = take(size_t(splits) * k * d * 4);
+    }
     L.table = take(k * (D / 2) * sizeof(float2));
     L.ints = take((4 * k + 1) * sizeof(int32_t));
     L.ft = take(ppk::first_token_workspace(c->dtype, g->k, c->vocab, c->d_model));
-    size_t gpart = 0;
-    if (split_width(c) && g->k <= 64) {
-        Proj p[4];
-        projections(c, p);
-        // O and down leave split-K partial sums (the tiles of 17 .. 64 prompts take as many
-        // splits as this holds)
-        gpart = std::max(size_t(ppk::skinny_split(p[1].N, p[1].K).splits) * k * p[1].N * 4,
-                         size_t(ppk::decode_gemm_splits(g->k, p[3].N, p[3].K)) * k * p[3].N * 4);
-    }
-    L.gpart = take(gpart);
     L.total = off;
     return L;
-}
-
-// How a step's projections run:
-//   kStream  up to 16 prompts at the widths they take: the weight-streaming kernels of k_decode.hip
-//   kTiles   up to 256: the prefill's GEMM tiles, O and down in up to `splits` K splits whose
-//            partial sums go to the workspace at `part`
-//   kWhole   the prefill's GEMMs as they are
-// The first two leave O's and down's partial sums to the norm that follows.  From 17 prompts on the
-// weights are no longer nearly all that a projection reads: the streaming kernels' wavefronts each
-// fetch every prompt's row, and O's workgroups each merge every prompt's attention chunks.  At 48
-// prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O, gate/up, down)
-// against 19 / 5 + 12 / 52 / 28 for the tiles (O with
-// its chunk merge as a kernel of its own).
-enum Mode { kStream, kTiles, kWhole };
-struct Plan {
-    Mode mode;
-    size_t part;
-    int splits;
-};
-Plan plan_of(const pp_config* c, const pp_gen_dlayout* g, const Layout& L) {
-    if (!split_width(c) || g->k > 256) return Plan{kWhole, 0, 0};
-    if (ppk::decode_stream_ok(g->k, c->d_model, c->n_heads * c->head_dim, c->ffn_dim)) return Plan{kStream, L.gpart, 0};
-    // past 64 prompts the partial sums take the place of the attention's chunk results, merged by
-    // then (two splits of d columns at least where H D >= d)
-    const size_t at = g->k <= 64 ? L.gpart : L.part, bytes = g->k <= 64 ? L.total - L.gpart : L.table - L.part;
-    const int splits = static_cast<int>(std::min<size_t>(bytes / (size_t(g->k) * c->d_model * 4), 16));
-    return splits > 0 ? Plan{kTiles, at, splits} : Plan{kWhole, 0, 0};
 }
 
 pp_status validate_layout(const pp_config* c, const pp_gen_dlayout* g) {
@@ -183,9 +182,10 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                                                                (g->ctx_rows + ppk::kDecodeChunk - 1) / ppk::kDecodeChunk + k));
     const ppk::DecodeLayout Ly{k, chunks(g->max_len), chunks(g->n_new), n_ctx_items, g->ctx_off, g->ctx_span,
                                g->ctx_valid, g->pos0, g->gen_off};
-    const Plan plan = plan_of(cfg, g, L);
-    const bool split = plan.mode != kWhole;
-    float* gpart = reinterpret_cast<float*>(ws + plan.part);
+    const Mode mode = mode_of(cfg, g);
+    const bool split = mode != kWhole;
+    const int splits = tile_splits(k);
+    float* gpart = reinterpret_cast<float*>(ws + L.gpart);
 
     // the split-K residual projections (O, down) leave their partial sums in gpart; the next
     // norm adds them to x (pending = their split count) before normalising
@@ -205,7 +205,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
         void* gk = static_cast<char*>(gen_k) + l * gen_layer;
         void* gv = static_cast<char*>(gen_v) + l * gen_layer;
         if (l > 0) norm(w->attn_norm[l], xn);
-        if (plan.mode == kStream) {
+        if (mode == kStream) {
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
             ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,
                              ppk::DecodeEpi{nullptr, 0, qo}, s);
@@ -218,8 +218,8 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
             ppk::qkv_rope_bf16(xn, d, w->wqkv[l], d, k, d, nullptr, 0, qo, s);
             ppk::decode_attention(dt, q, hd, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, attn, hd, s);
             if (split) {
-                ppk::gemm_partial_bf16(attn, hd, w->wo[l], hd, gpart, k, d, hd, plan.splits, s);
-                pending = ppk::gemm_partial_splits(k, d, hd, plan.splits);
+                ppk::gemm_partial_bf16(attn, hd, w->wo[l], hd, gpart, k, d, hd, splits, s);
+                pending = ppk::gemm_partial_splits(k, d, hd, splits);
             } else {
                 ppk::gemm_bf16(ppk::kResidual, attn, hd, w->wo[l], hd, x, d, k, d, hd, nullptr, 0, s);
             }
@@ -231,7 +231,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                           hd, x, d, k, d, hd, s);
         }
         norm(w->mlp_norm[l], xn);
-        if (plan.mode == kStream) {
+        if (mode == kStream) {
             const ppk::QkvOut none{};
             ppk::decode_gemm(ppk::kSwiGLU, xn, d, k, w->w_gateup[l], d, 2 * F, d, gpart,
                              ppk::DecodeEpi{act, F, none}, s);
@@ -241,8 +241,8 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
         } else if (bf) {
             ppk::gemm_bf16(ppk::kSwiGLU, xn, d, w->w_gateup[l], d, act, F, k, 2 * F, d, nullptr, 0, s);
             if (split) {
-                ppk::gemm_partial_bf16(act, F, w->w_down[l], F, gpart, k, d, F, plan.splits, s);
-                pending = ppk::gemm_partial_splits(k, d, F, plan.splits);
+                ppk::gemm_partial_bf16(act, F, w->w_down[l], F, gpart, k, d, F, splits, s);
+                pending = ppk::gemm_partial_splits(k, d, F, splits);
             } else {
                 ppk::gemm_bf16(ppk::kResidual, act, F, w->w_down[l], F, x, d, k, d, F, nullptr, 0, s);
             }

@@ -189,8 +189,7 @@ bool residual_rmsnorm_ok(int d);
 // residual_rmsnorm to add.
 void decode_gemm(int epi, const void* A, int64_t lda, int k, const void* W, int64_t ldw, int N, int K, float* part,
                  const DecodeEpi& ep, hipStream_t s);
-// The number of K splits decode_gemm's kResidual leaves for k <= 16 rows of an N x K product (for
-// more rows, what the workspace's room for partial sums is sized by).
+// The number of K splits decode_gemm's kResidual leaves for k <= 16 rows of an N x K product.
 int decode_gemm_splits(int k, int N, int K);
 
 }  // namespace ppk

@@ -105,7 +105,7 @@ WIDE = {"d5120": dict(d_model=5120, n_heads=40, n_kv_heads=40, ffn_dim=13824),
         "f5248": dict(d_model=2048, n_heads=16, n_kv_heads=16, ffn_dim=5248),
         # a width the weight-streaming kernels do not take: GEMM tiles at any prompt count
         "d1024": dict(d_model=1024, n_heads=8, n_kv_heads=4, ffn_dim=2816),
-        # H D < d: the partial sums of more than 64 prompts have room for one K split only
+        # H D < d: O's K is shorter than the row
         "h2": dict(d_model=1024, n_heads=2, n_kv_heads=2, ffn_dim=1024)}
 
 
@@ -218,6 +218,40 @@ def test_packed_and_padded_generation_are_bit_identical(model_name, lengths, n_l
                 assert np.array_equal(_gen_rows(packed, l, i, n_new, which), _gen_rows(padded, l, i, n_new, which))
     # the full-batching cache is larger by the padding of every prompt to the longest
     assert padded.kv_cache_bytes() > packed.kv_cache_bytes()
+
+
+@pytest.mark.parametrize("model_name,lengths,n_layers", [
+    ("d1024", [3] * 70, 2),                                           # partial sums past 64 prompts
+    ("llama-1.3b", [2, 1] * 65, 1),
+    ("h2", [2, 1] * 40, 2),                                           # H D < d
+    ("d1024", [3] * 20, 2),
+    ("d1024", [3] * 10, 2),
+])
+def test_a_steps_bits_do_not_depend_on_room_or_on_other_prompts(model_name, lengths, n_layers):
+    """Room for more generated tokens, or another prompt's length, changes no bit of a prompt's step."""
+    def step(lens, n_new):
+        case = _bf16_case(model_name, lens, n_layers, seed=3)
+        lm_head = W.draw_lm_head(case.wl, 3, case.shape)
+        case.tokens[:] = np.arange(case.tokens.size) % 97             # the same prompts whatever follows them
+        model, pre, lm, _ = _prefill(case, lm_head)
+        gen = pp.Generation(model, pre, case.lengths, n_new)
+        k = len(lens)
+        logits = torch.empty((k, case.shape.vocab), dtype=torch.float32, device="cuda")
+        out = torch.empty(k, dtype=torch.int32, device="cuda")
+        res = []
+        for t in range(2):
+            gen.step(t, i32_dev(np.arange(k) + 5 * t), lm, out, logits)
+            res.append(logits.clone())
+        torch.cuda.synchronize()
+        return res + [torch.stack([gen.gen_k[l, int(r):int(r) + 2] for l in range(n_layers) for r in gen.layout.gen_off])]
+
+    want = step(lengths, 2)
+    assert bool(torch.isfinite(want[1]).all())
+    for n_new in (129, 300):
+        for a, b in zip(want, step(lengths, n_new)):
+            assert torch.equal(a, b), n_new
+    for a, b in zip(want[:2], step(lengths[:-1] + [400], 2)[:2]):
+        assert torch.equal(a[:-1], b[:-1])
 
 
 def test_generate_equals_steps_one_by_one():
