@@ -312,7 +312,7 @@ __device__ __forceinline__ void decode_attn_chunk_bf16(
         m[e] = fmaxf(sc[0][e], sc[1][e]);
 #pragma unroll
         for (int x = 1; x < 16; x <<= 1) m[e] = fmaxf(m[e], __shfl_xor(m[e], x));
-        const float mm = m[e] == -INFINITY ? 0.f : m[e];   // no key: every probability 0
+        const float mm = m[e] == -INFINITY ? 0.f : m[e];   // no key, or none above -inf: every probability 0
         float p[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) p[b] = exp2f(sc[b][e] - mm);
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __rest
         for (int e = 0; e < E; ++e) o2[e] = pp[lane * E + e];
         merge<E>(m, l, o, pp[D], pp[D + 1], o2);
     }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const float inv = 1.f / l;           // l = 0 only where every score is -inf: not a number, as softmax
     T* dst = out + int64_t(i) * ldo + int64_t(h) * D + lane * E;
 #pragma unroll
     for (int e = 0; e < E; ++e) dst[e] = static_cast<T>(o[e] * inv);
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void o_proj_kernel(int k, const bf16* __restri
                 load8(pp + ch * 8, o2);
                 merge<8>(mm, ll, o, pp[128], pp[129], o2);
             }
-            const float inv = ll > 0.f ? 1.f / ll : 0.f;
+            const float inv = 1.f / ll;   // as decode_combine_kernel
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = static_cast<bf16>(o[e] * inv);
         }

@@ -14,6 +14,8 @@ against the generation oracle (full recomputation per token, section 2.2).
 * the packed and the full-batching layouts give bit-identical tokens and generated rows,
   and pp_generate is bit-identical to the same steps taken one by one.
 """
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -252,6 +254,35 @@ def test_a_steps_bits_do_not_depend_on_room_or_on_other_prompts(model_name, leng
             assert torch.equal(a, b), n_new
     for a, b in zip(want[:2], step(lengths[:-1] + [400], 2)[:2]):
         assert torch.equal(a[:-1], b[:-1])
+
+
+def test_scores_of_minus_infinity():
+    """Keys whose score is -inf weigh nothing, and a row with no other key is not a number (the
+    softmax of a row of -inf).  wk = -wq, so the step's own key is the negative of its query; a
+    context of that key gives -|q|^2 = -inf everywhere, a key of zeros scores 0."""
+    for k in (4, 20):                                                 # O merges the chunks; the tiles
+        case = _bf16_case("llama-1.3b", [1, 5, 200, 300] * (k // 4), 1, seed=5)
+        layer = case.weights["layers"][0]
+        layer["wq"] = layer["wq"] * np.float32(1e22)
+        layer["wk"] = -layer["wq"]
+        lm = bf16_dev(W.draw_lm_head(case.wl, 5, case.shape))
+        model = pp.DeviceModel(case.shape, case.weights)
+        L, kvw = int(case.lengths.sum()), case.shape.n_kv_heads * case.shape.head_dim
+        ctx_k = torch.zeros((1, L, kvw), dtype=torch.bfloat16, device="cuda")
+        ctx_v = torch.ones_like(ctx_k)
+        gen = pp.Generation(model, types.SimpleNamespace(k_cache=ctx_k, v_cache=ctx_v), case.lengths, 1)
+        toks, out = i32_dev(np.arange(k) + 3), torch.empty(k, dtype=torch.int32, device="cuda")
+        logits = torch.empty((k, case.shape.vocab), dtype=torch.float32, device="cuda")
+        gen.step(0, toks, lm, out, logits)                            # the step's keys
+        off = gen.layout.ctx_off
+        for i in range(k):
+            ctx_k[0, off[i]:off[i] + int(case.lengths[i])] = gen.gen_k[0, i]
+        ctx_k[0, off[3] + 150] = 0                                    # prompt 3: one key of score 0
+        gen.step(0, toks, lm, out, logits)
+        torch.cuda.synchronize()
+        nan = torch.isnan(logits).all(1).cpu().numpy()
+        assert nan.tolist() == [i != 3 for i in range(k)], (k, nan)
+        assert bool(torch.isfinite(logits[3]).all()) and out.cpu().tolist()[:3] == [-1, -1, -1]
 
 
 def test_generate_equals_steps_one_by_one():
