@@ -331,6 +331,9 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_kernel(const bf16* __restrict
 }
 
 // ----------------------------------------------------------------------------- float32
+// 16 bytes at any float: the caches of pp_attention need no more alignment than that.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // One wavefront per (query slot, head), keys in tiles of 64: lane j holds key j's score (its own
 // dot product over the head, so no reduction across lanes per key), one maximum and one sum across
 // the lanes per tile, then lane d accumulates dims d (and d + 64) over the tile's keys, the
@@ -374,7 +377,7 @@ __global__ __launch_bounds__(NT) void attn_f32_kernel(const float* __restrict__ 
                 const float* k = K + int64_t(j) * ldkv;
 #pragma unroll
                 for (int c = 0; c < D; c += 4) {
-                    const f32x4 kk = *reinterpret_cast<const f32x4*>(k + c);
+                    const f32x4 kk = *reinterpret_cast<const f32x4_a4*>(k + c);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) d4[e] = fmaf(qr[c + e], kk[e], d4[e]);
                 }

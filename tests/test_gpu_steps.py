@@ -329,6 +329,29 @@ def test_attention_f32_key_tiles(lengths, H, Hkv, Dh, padded):
     assert report(f"attention f32 {lengths} padded={padded}", got[span], ref[span])[0] <= 1e-5
 
 
+@pytest.mark.parametrize("Dh,H,Hkv", [(64, 4, 2), (128, 2, 2)])
+def test_attention_f32_buffers_at_any_float(Dh, H, Hkv):
+    """Queries, caches and output one float past a 16-byte boundary give the same bits."""
+    plan = pp.pp_pack([70, 3, 1, 200], 256)
+    rng = np.random.default_rng(Dh)
+    a = _attn_inputs(plan, rng, H, Hkv, Dh, 1.0, pp.PP_F32)
+    dplan, cfg = pp.DevicePlan(plan), _cfg(H, Hkv, d=256, F=688, dtype=pp.PP_F32, D_=Dh)
+
+    def run(shift):
+        def at(x):
+            t = torch.zeros(x.size + 4, dtype=torch.float32, device="cuda")[shift:shift + x.size].view(x.shape)
+            return t.copy_(f32_dev(x))
+        q, kc, vc, out = (at(np.asarray(x, dtype=np.float32)) for x in (a[0], a[1], a[2], np.zeros((plan.n_slots, H * Dh))))
+        assert all(t.data_ptr() % 16 == 4 * shift for t in (q, kc, vc, out))
+        pp.pp_attention(cfg, dplan, q, H * Dh, kc, vc, out)
+        return host64(out)
+
+    want = run(0)
+    assert np.isfinite(want).all() and np.abs(want).max() > 0
+    for shift in (1, 2, 3):
+        assert np.array_equal(run(shift), want)
+
+
 # ----------------------------------------------------------------------------- fused QKV projection
 QKV_CASES = [
     # lengths, capacity (None: full batching), H, Hkv, d, theta
