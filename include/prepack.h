@@ -227,9 +227,11 @@ pp_status pp_prefill(const pp_config* cfg, const pp_weights* w, const pp_dplan* 
                      float* hidden, void* k_cache, void* v_cache, void* stream);
 
 /* ------------------------------------------------------------------------------------------
- * Single steps of pp_prefill.  Each computes the values of that step of pp_prefill (which
- * joins some of them in one launch) on caller device buffers, for callers that assemble their own layer loop and for
- * step-by-step verification.  Same conventions: validated before enqueuing, asynchronous.
+ * Single steps of pp_prefill.  Each computes the values of that step of pp_prefill (which joins
+ * some of them in one launch) bit for bit, on caller device buffers, for callers that assemble
+ * their own layer loop and for step-by-step verification (the QKV step in bf16 is
+ * pp_qkv_projection; in float32 pp_gemm, pp_rope and pp_kv_scatter).  Same conventions:
+ * validated before enqueuing, asynchronous.
  * `rows` buffers are row-major with the stated row length; `plan` is a device plan.
  * ---------------------------------------------------------------------------------------- */
 

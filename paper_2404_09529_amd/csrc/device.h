@@ -54,3 +54,10 @@ __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x));
 // SiLU with the hardware reciprocal (1 ulp) in place of the correctly rounded division: for
 // results that are rounded to bf16 (8 significant bits) the difference is invisible.
 __device__ __forceinline__ float silu_rcp(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+
+// One rotate-half pair (x, y) at angle (c, s): the products are fused in a fixed order.
+__device__ __forceinline__ float rope_lo(float x, float y, float c, float s) { return fmaf(x, c, -(y * s)); }
+__device__ __forceinline__ float rope_hi(float x, float y, float c, float s) { return fmaf(x, s, y * c); }
+// The upper half as pp_rope and the float32 QKV epilogue form it: a float32 prefill's caches are
+// those of pp_gemm, pp_rope and pp_kv_scatter bit for bit.
+__device__ __forceinline__ float rope_hi_step(float x, float y, float c, float s) { return fmaf(y, c, x * s); }

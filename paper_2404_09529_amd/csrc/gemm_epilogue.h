@@ -6,10 +6,6 @@
 #include "device.h"
 #include "kernels.h"
 
-// One rotate-half pair (x, y) at angle (c, s): the products are fused in a fixed order.
-__device__ __forceinline__ float rope_lo(float x, float y, float c, float s) { return fmaf(x, c, -(y * s)); }
-__device__ __forceinline__ float rope_hi(float x, float y, float c, float s) { return fmaf(x, s, y * c); }
-
 // The epilogue of one wavefront's NB x MB blocks, stored straight from the registers.  In block
 // (i, j) lane l holds activation row mb + 16 j + l % 16 and 4 consecutive weight rows of block i,
 // 4 (l / 16) + 0..3.  The wavefront is the wn-th along N of a tile whose first weight row is n0;

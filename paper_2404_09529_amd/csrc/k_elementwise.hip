@@ -297,8 +297,8 @@ __global__ __launch_bounds__(kBlock) void rope_kernel(T* __restrict__ qkv, int64
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float2 t = cs[i];
-        na[i] = a[i] * t.x - b[i] * t.y;
-        nb[i] = b[i] * t.x + a[i] * t.y;
+        na[i] = rope_lo(a[i], b[i], t.x, t.y);
+        nb[i] = rope_hi_step(a[i], b[i], t.x, t.y);
     }
     store8(base, na);
     store8(base + half, nb);

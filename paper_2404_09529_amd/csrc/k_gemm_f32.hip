@@ -109,7 +109,7 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(const float* __restrict__ 
             for (int e = 0; e < 4; ++e) {
                 const float x = v[0][e], y = v[1][e];
                 v[0][e] = rope_lo(x, y, cs[e].x, cs[e].y);
-                v[1][e] = rope_hi(x, y, cs[e].x, cs[e].y);
+                v[1][e] = rope_hi_step(x, y, cs[e].x, cs[e].y);
             }
         }
         const int row = kind == 0 ? m : qo.slot_kv[m];

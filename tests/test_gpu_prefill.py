@@ -24,7 +24,7 @@ from oracle import decoder as D
 from paper_2404_09529_amd import prepack as pp
 from paper_2404_09529_amd import workloads as W
 
-from .gpu_util import gate_vs_floor, gpu_prefill, i32_dev, oracle_weights, report, require_gpu
+from .gpu_util import gate_vs_floor, gpu_prefill, host64, i32_dev, oracle_weights, report, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -80,6 +80,27 @@ def test_fp32_fused_qkv_head_sizes(H, Hkv, Dh):
         assert mx <= 1e-4 and mean <= 1e-5
     for a, b in zip([packed[0], *packed[1], *packed[2]], [padded[0], *padded[1], *padded[2]]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("H,Hkv,Dh", [(4, 4, 64), (2, 1, 128)])
+def test_fp32_caches_are_the_single_steps(H, Hkv, Dh):
+    """The first layer's caches of a float32 pp_prefill are those of pp_embed, pp_rmsnorm, pp_gemm,
+    pp_rope and pp_kv_scatter bit for bit."""
+    case = W.make_case(1, 6, lengths=np.array([70, 3, 40, 1, 300]), capacity=320, random_gains=True, n_layers=1,
+                       n_heads=H, n_kv_heads=Hkv, head_dim=Dh, ffn_dim=304)
+    plan = pp.pp_pack(case.lengths, case.capacity)
+    _, k, v = gpu_prefill(case, plan)
+    model, dplan, s = pp.DeviceModel(case.shape, case.weights), pp.DevicePlan(plan), case.shape
+    T, d, qkv_w, kvw = plan.n_slots, s.d_model, (H + 2 * Hkv) * Dh, Hkv * Dh
+    f32 = lambda *shape: torch.zeros(shape, dtype=torch.float32, device="cuda")      # noqa: E731
+    x, xn, qkv, table = f32(T, d), f32(T, d), f32(T, qkv_w), f32(plan.max_len * Dh)
+    kc, vc = f32(plan.total_len, kvw), f32(plan.total_len, kvw)
+    pp.pp_embed(pp.PP_F32, model.embed, s.vocab, d, i32_dev(case.tokens), dplan, x)
+    pp.pp_rmsnorm(pp.PP_F32, x, model.layers[0]["attn_norm"], T, d, s.rms_eps, xn)
+    pp.pp_gemm(pp.PP_F32, pp.PP_EPI_STORE, xn, d, model.layers[0]["wqkv"], d, qkv, qkv_w, T, qkv_w, d)
+    pp.pp_rope(model.config, dplan, qkv, table)
+    pp.pp_kv_scatter(model.config, dplan, qkv, kc, vc)
+    assert np.array_equal(host64(kc), k[0]) and np.array_equal(host64(vc), v[0])
 
 
 def test_tiny_fp32_deeper_model():
