@@ -174,6 +174,10 @@ void rmsnorm_dispatch(const float* x, const float* g, TO* out, const int32_t* sl
 // tokens: 115 + 115 -> 150 us).  The first table_blocks workgroups fill the table, the others take
 // kRowsPerBlock rows each.  A lane's share of a row and the order of the sum are rmsnorm_kernel's,
 // so xn is the same bit for bit.
+// NC > 0: rows of up to NC * 256 elements, in registers, every load requested before the first use
+// (WHOLE: exactly NC * 256; else a lane past the row adds nothing to the sum).  A row read twice by a loop that waits
+// for each load took a decode step's first launch at d 6144 25 us, at d 3072 14; registers 6 and 5.
+// NC == 0: longer rows.
 struct TableArgs {
     float2* table;
     int64_t n;              // entries
@@ -186,7 +190,7 @@ struct TableArgs {
     int32_t *slot_pos, *slot_kv;
 };
 
-template <typename TE, int NC>
+template <typename TE, int NC, bool WHOLE>
 __global__ __launch_bounds__(kBlock) void start_kernel(float* __restrict__ x, const TE* __restrict__ E,
                                                        const int32_t* __restrict__ tokens,
                                                        const int32_t* __restrict__ slot_kv, int T, int d, int vocab,
@@ -216,24 +220,27 @@ __global__ __launch_bounds__(kBlock) void start_kernel(float* __restrict__ x, co
     TE* yr = xn + row * d;
     float ss = 0.f;
     if constexpr (NC > 0) {
+        // a lane past the row takes its last four elements again (the same values stored twice)
+        auto at = [&](int c) { return WHOLE ? c * 256 + lane * 4 : min(c * 256 + lane * 4, d - 4); };
         f32x4 v[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) v[c] = load4(er + c * 256 + lane * 4);
+        for (int c = 0; c < NC; ++c) v[c] = load4(er + at(c));
         if (tok < 0) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c] = f32x4{};
         }
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            store4(xr + c * 256 + lane * 4, v[c]);
-            ss += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
+            store4(xr + at(c), v[c]);
+            const float q = v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
+            ss += WHOLE || c * 256 + lane * 4 < d ? q : 0.f;
         }
         ss = wave_sum(ss);
         const float scale = rsqrtf(ss / static_cast<float>(d) + eps);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const f32x4 gg = *reinterpret_cast<const f32x4*>(g + c * 256 + lane * 4);
-            store4(yr + c * 256 + lane * 4, v[c] * scale * gg);
+            const f32x4 gg = *reinterpret_cast<const f32x4*>(g + at(c));
+            store4(yr + at(c), v[c] * scale * gg);
         }
     } else {
         for (int c = lane * 4; c < d; c += 256) {
@@ -257,18 +264,20 @@ void start_dispatch(float* x, const TE* E, const int32_t* tokens, const int32_t*
     const unsigned tb = static_cast<unsigned>((ta.n + kBlock - 1) / kBlock);
     const unsigned grid = tb + (T + kRowsPerBlock - 1) / kRowsPerBlock;
     if (grid == 0) return;
-    const int nc = d % 256 == 0 ? d / 256 : 0;
-#define PP_START(NC) start_kernel<TE, NC><<<grid, kBlock, 0, s>>>(x, E, tokens, slot_kv, T, d, vocab, g, xn, eps, tb, ta)
-    switch (nc) {
-        case 1: PP_START(1); break;
-        case 2: PP_START(2); break;
-        case 4: PP_START(4); break;
-        case 8: PP_START(8); break;
-        case 16: PP_START(16); break;
-        case 20: PP_START(20); break;
-        case 32: PP_START(32); break;
-        default: PP_START(0); break;
-    }
+    const int nc = (d + 255) / 256;
+#define PP_START(NC, WHOLE) \
+    start_kernel<TE, NC, WHOLE><<<grid, kBlock, 0, s>>>(x, E, tokens, slot_kv, T, d, vocab, g, xn, eps, tb, ta)
+#define PP_START_UP_TO(NC) \
+    if (nc <= NC) return d == NC * 256 ? PP_START(NC, true) : PP_START(NC, false)
+    PP_START_UP_TO(1);
+    PP_START_UP_TO(2);
+    PP_START_UP_TO(4);
+    PP_START_UP_TO(8);
+    PP_START_UP_TO(16);
+    PP_START_UP_TO(20);
+    PP_START_UP_TO(32);
+    PP_START(0, false);
+#undef PP_START_UP_TO
 #undef PP_START
 }
 

@@ -82,12 +82,14 @@ def test_fp32_fused_qkv_head_sizes(H, Hkv, Dh):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("H,Hkv,Dh", [(4, 4, 64), (2, 1, 128)])
-def test_fp32_caches_are_the_single_steps(H, Hkv, Dh):
+# d below, at and past the row lengths that the first launch holds in registers
+@pytest.mark.parametrize("H,Hkv,Dh,d", [(4, 4, 64, 256), (2, 1, 128, 256), (4, 2, 64, 80), (2, 1, 64, 272), (1, 1, 64, 1040),
+                                        (1, 1, 64, 8208)])
+def test_fp32_caches_are_the_single_steps(H, Hkv, Dh, d):
     """The first layer's caches of a float32 pp_prefill are those of pp_embed, pp_rmsnorm, pp_gemm,
     pp_rope and pp_kv_scatter bit for bit."""
     case = W.make_case(1, 6, lengths=np.array([70, 3, 40, 1, 300]), capacity=320, random_gains=True, n_layers=1,
-                       n_heads=H, n_kv_heads=Hkv, head_dim=Dh, ffn_dim=304)
+                       d_model=d, n_heads=H, n_kv_heads=Hkv, head_dim=Dh, ffn_dim=304)
     plan = pp.pp_pack(case.lengths, case.capacity)
     _, k, v = gpu_prefill(case, plan)
     model, dplan, s = pp.DeviceModel(case.shape, case.weights), pp.DevicePlan(plan), case.shape
@@ -101,6 +103,27 @@ def test_fp32_caches_are_the_single_steps(H, Hkv, Dh):
     pp.pp_rope(model.config, dplan, qkv, table)
     pp.pp_kv_scatter(model.config, dplan, qkv, kc, vc)
     assert np.array_equal(host64(kc), k[0]) and np.array_equal(host64(vc), v[0])
+
+
+@pytest.mark.parametrize("d", [256, 768, 3072, 6144, 8448])
+def test_bf16_caches_are_the_single_steps(d):
+    """The first layer's caches of a bf16 pp_prefill, with a token id outside the vocabulary, are those
+    of pp_embed, pp_rmsnorm and pp_qkv_projection bit for bit."""
+    case = W.make_case(1, 7, lengths=np.array([70, 3, 40, 1, 300]), capacity=320, random_gains=True, n_layers=1, dtype="bf16",
+                       d_model=d, n_heads=2, n_kv_heads=1, head_dim=128, ffn_dim=256)
+    case.tokens[5] = case.shape.vocab + 3
+    plan = pp.pp_pack(case.lengths, case.capacity)
+    _, k, v = gpu_prefill(case, plan)
+    model, dplan, s = pp.DeviceModel(case.shape, case.weights), pp.DevicePlan(plan), case.shape
+    T = plan.n_slots
+    half = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16, device="cuda")      # noqa: E731
+    x, table = torch.zeros((T, d), device="cuda"), torch.zeros(plan.max_len * 128, device="cuda")
+    xn, q, kc, vc = half(T, d), half(T, 256), half(plan.total_len, 128), half(plan.total_len, 128)
+    pp.pp_embed(pp.PP_BF16, model.embed, s.vocab, d, i32_dev(case.tokens), dplan, x)
+    pp.pp_rmsnorm(pp.PP_BF16, x, model.layers[0]["attn_norm"], T, d, s.rms_eps, xn)
+    pp.pp_qkv_projection(model.config, dplan, xn, model.layers[0]["wqkv"], table, q, kc, vc)
+    assert np.array_equal(host64(kc), k[0]) and np.array_equal(host64(vc), v[0])
+    assert np.all(v[0][5] == 0) and np.abs(v[0]).max() > 0
 
 
 def test_tiny_fp32_deeper_model():
