@@ -108,7 +108,9 @@ WIDE = {"d5120": dict(d_model=5120, n_heads=40, n_kv_heads=40, ffn_dim=13824),
         # a width the weight-streaming kernels do not take: GEMM tiles at any prompt count
         "d1024": dict(d_model=1024, n_heads=8, n_kv_heads=4, ffn_dim=2816),
         # H D < d: O's K is shorter than the row
-        "h2": dict(d_model=1024, n_heads=2, n_kv_heads=2, ffn_dim=1024)}
+        "h2": dict(d_model=1024, n_heads=2, n_kv_heads=2, ffn_dim=1024),
+        # eight query heads per key/value head
+        "r8": dict(d_model=2048, n_heads=16, n_kv_heads=2, ffn_dim=2816)}
 
 
 def _bf16_case(model_name, lengths, n_layers, seed=0):
@@ -135,6 +137,11 @@ def _bf16_case(model_name, lengths, n_layers, seed=0):
     ("f5248", [9, 130, 1], 1, 2),
 ])
 def test_bf16_decode_steps_teacher_forced(model_name, lengths, n_layers, n_new):
+    _teacher_forced(model_name, lengths, n_layers, n_new, range(len(lengths)))
+
+
+def _teacher_forced(model_name, lengths, n_layers, n_new, picks):
+    """Every step fed the oracle's tokens; the prompts in ``picks`` compared with the oracle."""
     case = _bf16_case(model_name, lengths, n_layers)
     lm_head = W.draw_lm_head(case.wl, 0, case.shape)
     sh = D.Shape.of(case.shape)
@@ -144,21 +151,23 @@ def test_bf16_decode_steps_teacher_forced(model_name, lengths, n_layers, n_new):
     gen = pp.Generation(model, pre, case.lengths, n_new)
     prompts = _prompts(case)
     w64, lm64 = oracle_weights(case.weights), lm_head.astype(np.float64)
-    fed = np.stack([G.generate(p, w64, sh, lm64, n_new + 1) for p in prompts])   # oracle's greedy
-    ref = [G.teacher_forced(p, fed[i, :n_new], w64, sh, lm64) for i, p in enumerate(prompts)]
-    flo = [G.teacher_forced(p, fed[i, :n_new], w64, sh, lm64, rnd=D.round_bf16)
-           for i, p in enumerate(prompts)]
+    fed = np.random.default_rng(k).integers(0, V, (k, n_new + 1))   # prompts that are not compared: any tokens
+    for i in picks:
+        fed[i] = G.generate(prompts[i], w64, sh, lm64, n_new + 1)   # oracle's greedy
+    ref = {i: G.teacher_forced(prompts[i], fed[i, :n_new], w64, sh, lm64) for i in picks}
+    flo = {i: G.teacher_forced(prompts[i], fed[i, :n_new], w64, sh, lm64, rnd=D.round_bf16) for i in picks}
+    rows = np.asarray(list(picks))
     logits = torch.empty((k, V), dtype=torch.float32, device="cuda")
     out = torch.empty(k, dtype=torch.int32, device="cuda")
     for t in range(n_new):
         gen.step(t, i32_dev(fed[:, t]), lm, out, logits)
         lg = host64(logits)
         tok = out.cpu().numpy()
-        # the step's logits [k, V] are one tensor of the gate
-        want_t = np.stack([ref[i].logits[t] for i in range(k)])
-        floor_t = np.stack([flo[i].logits[t] for i in range(k)])
-        gate_vs_floor(f"{model_name} step {t} logits", [D.errors(lg, want_t)], [D.errors(floor_t, want_t)])
-        for i in range(k):
+        # the step's logits [picks, V] are one tensor of the gate
+        want_t = np.stack([ref[i].logits[t] for i in picks])
+        floor_t = np.stack([flo[i].logits[t] for i in picks])
+        gate_vs_floor(f"{model_name} step {t} logits", [D.errors(lg[rows], want_t)], [D.errors(floor_t, want_t)])
+        for i in picks:
             want = ref[i].logits[t]
             err = np.abs(lg[i] - want)
             slack = 2 * err.max()
@@ -170,7 +179,7 @@ def test_bf16_decode_steps_teacher_forced(model_name, lengths, n_layers, n_new):
     for l in range(n_layers):
         for which in ("k", "v"):
             errs = []
-            for i in range(k):
+            for i in picks:
                 got = _gen_rows(gen, l, i, n_new, which)
                 want = (ref[i].k if which == "k" else ref[i].v)[l]
                 floor = (flo[i].k if which == "k" else flo[i].v)[l]
@@ -196,6 +205,24 @@ def test_bf16_decode_steps_on_gemm_tiles(model_name, lengths, n_layers, n_new):
 
 
 @pytest.mark.parametrize("model_name,lengths,n_layers,n_new", [
+    # two layers: a layer's partial sums lie where the attention of the next writes its chunks
+    ("d1024", [4, 9, 1, 33] * 5, 2, 2),
+    ("d1024", [3, 1, 130] * 23, 2, 2),                                # 69 prompts
+    ("d1024", [2, 5, 1] * 50, 2, 1),                                  # 150
+    # the 128-row tiles of the split projections at real widths (O, down): 128 x 64 and 128 x 128
+    ("llama2-7b", [2, 5, 1, 1, 3] * 14, 1, 1),                        # 70 prompts
+    ("llama2-7b", [1, 2, 1] * 43, 1, 1),                              # 129: 128 x 128 and 128 x 256
+    # eight query heads per key/value head: 10 prompts streamed, 20 on the tiles
+    ("r8", [40, 1, 300, 9, 130] * 2, 1, 2),
+    ("r8", [40, 1, 300, 9, 130] * 4, 1, 2),
+])
+def test_bf16_decode_steps_sampled(model_name, lengths, n_layers, n_new):
+    """Larger steps: the prompts at the ends and around the row tiles' edges compared."""
+    k = len(lengths)
+    _teacher_forced(model_name, lengths, n_layers, n_new, sorted({0, 1, 2, 15, 31, 32, 63, 64, 127, 128, k - 1} & set(range(k))))
+
+
+@pytest.mark.parametrize("model_name,lengths,n_layers,n_new", [
     ("llama-1.3b", [1, 300, 7, 129, 1, 64], 1, 5),
     ("mistral-7b", [700, 2, 33], 1, 5),
     ("d5120", [2, 150, 9], 1, 5),
@@ -203,6 +230,11 @@ def test_bf16_decode_steps_on_gemm_tiles(model_name, lengths, n_layers, n_new):
     # past 128 generated tokens: two chunks of generated keys per prompt (the packed layout's
     # attention work list against the full-batching layout's direct grid)
     ("llama-1.3b", [3, 260, 1, 40], 1, 140),
+    # on the tiles: partial sums in K splits, 17 prompts and more
+    ("d1024", [1, 140, 7, 2] * 5, 2, 4),
+    ("d1024", [1, 140, 7, 2, 30] * 14, 2, 4),
+    ("llama-1.3b", [2, 1, 9] * 43, 1, 3),
+    ("r8", [3, 200, 1, 40], 2, 4),
 ])
 def test_packed_and_padded_generation_are_bit_identical(model_name, lengths, n_layers, n_new):
     case = _bf16_case(model_name, lengths, n_layers, seed=1)
