@@ -13,9 +13,9 @@
 //              the residual adds of O and down happen in the norm that follows each
 //   final rmsnorm -> LM head and greedy choice (the first-token kernels, one row per prompt).
 // The projections: for bf16 steps of up to 16 prompts, weight-streaming GEMMs for one row
-// per prompt (QKV and gate/up with their epilogues in the kernel; O and down as split-K
-// partial sums that the next norm adds); up to 256 prompts the prefill's GEMM tiles, O and down
-// split likewise; otherwise the prefill's GEMM kernels with M = k.
+// per prompt at the widths where they are faster (QKV and gate/up with their epilogues in the
+// kernel; O and down as split-K partial sums that the next norm adds); up to 256 prompts the
+// prefill's GEMM tiles, O and down split likewise; otherwise the prefill's GEMM kernels with M = k.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,21 +51,36 @@ void projections(const pp_config* c, Proj (&p)[4]) {
 // bf16 widths whose O and down projections may leave partial sums to the residual norm.
 bool split_width(const pp_config* c) { return c->dtype == PP_BF16 && ppk::residual_rmsnorm_ok(c->d_model); }
 
-// How a step's projections run:
-//   kStream  up to 16 prompts at the widths they take: the weight-streaming kernels of k_decode.hip
-//   kTiles   up to 256: the prefill's GEMM tiles, O and down in up to tile_splits(k) K splits
-//   kWhole   the prefill's GEMMs as they are
-// The first two leave O's and down's partial sums to the norm that follows.  From 17 prompts on the
-// weights are no longer nearly all that a projection reads: the streaming kernels' wavefronts each
-// fetch every prompt's row, and O's workgroups each merge every prompt's attention chunks.  At 48
-// prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O, gate/up, down)
-// against 19 / 5 + 12 / 52 / 28 for the tiles (O with
-// its chunk merge as a kernel of its own).
-enum Mode { kStream, kTiles, kWhole };
+// How a step's projections run.  Up to 16 prompts take the weight-streaming kernels of k_decode.hip
+// where those are the faster ones, projection by projection; up to 256 the prefill's GEMM tiles, O
+// and down in K splits; more, and widths that the residual norm does not take, the prefill's GEMMs
+// as they are.
+// From 17 prompts on the weights are no longer nearly all that a projection reads: the streaming
+// kernels' wavefronts each fetch every prompt's row, and O's workgroups each merge every prompt's
+// attention chunks.  At 48 prompts of a grouped-query 7B layer they took 23 / 30 / 90 / 50 us (QKV, O,
+// gate/up, down) against 19 / 5 + 12 / 52 / 28 for the tiles (O with its chunk merge as a kernel of its own).
+struct Plan {
+    bool split;    // O and down leave partial sums to the norm that follows
+    bool paired;   // QKV and gate/up streamed
+    bool o;        // O streamed, merging the attention's chunks
+    bool down;     // down streamed
+};
 constexpr int kSplitPrompts = 256;
-Mode mode_of(const pp_config* c, const pp_gen_dlayout* g) {
-    if (!split_width(c) || g->k > kSplitPrompts) return kWhole;
-    return ppk::decode_stream_ok(g->k, c->d_model, c->n_heads * c->head_dim, c->ffn_dim) ? kStream : kTiles;
+Plan plan_of(const pp_config* c, int k) {
+    const int d = c->d_model;
+    Plan p{split_width(c) && k <= kSplitPrompts, false, false, false};
+    if (!p.split || k > 16) return p;
+    // QKV and gate/up where a row is a power of two of the 512-column segments (or half a one): a
+    // step of two layers at d 512 on the tiles 82 us, streamed 71; d 1024: 109 and 102.
+    // O and down, the same step with both on the tiles, down streamed, O streamed, both streamed (QKV
+    // and gate/up on the tiles): d 1024, 1 prompt: 126, 121, 114, 109 us; d 3072: 240, 227, 224, 212;
+    // d 5120: 413, 400, 402, 387, and at 16 prompts, every one of which each of O's workgroups
+    // merges, 438, 434, 448, 446; d 6144: 522, 489, 518, 483, and at 10 prompts 536, 503, 546, 509;
+    // d 8192, one layer: 471, 475, 475, 477.
+    p.paired = ppk::decode_paired_ok(d);
+    p.o = d <= 4096 || (d <= 6144 && k * d <= 32768);
+    p.down = d <= 6144;
+    return p;
 }
 
 // The K splits that the tiles may take for O and down: 16 up to 128 prompts, fewer for more (2048 rows
@@ -95,18 +110,19 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.act = take(k * F * e);
     L.h = take(k * d * 4);   // no longer used; the documented size of a workspace holds it
     const size_t chunk_bytes = k * size_t(c->n_heads) * nch * (D + 4) * 4;
-    const Mode mode = mode_of(c, g);
-    if (mode == kTiles) {   // the chunk results are merged before O leaves its first partial sum
-        L.part = L.gpart = take(std::max(chunk_bytes, size_t(tile_splits(g->k)) * k * d * 4));
-    } else {
-        L.part = take(chunk_bytes);
-    }
-    if (mode == kStream) {  // O merges them while it leaves its partial sums
+    const Plan plan = plan_of(c, g->k);
+    if (plan.split) {
         Proj p[4];
         projections(c, p);
-        const int splits = std::max(ppk::skinny_split(p[1].N, p[1].K).splits,
-                                    ppk::decode_gemm_splits(g->k, p[3].N, p[3].K));
-        L.gpart = take(size_t(splits) * k * d * 4);
+        int splits = plan.o && plan.down ? 0 : tile_splits(g->k);
+        if (plan.o) splits = std::max(splits, ppk::skinny_split(p[1].N, p[1].K).splits);
+        if (plan.down) splits = std::max(splits, ppk::decode_gemm_splits(g->k, p[3].N, p[3].K));
+        const size_t sums = size_t(splits) * k * d * 4;
+        // a streamed O merges the chunk results while it leaves its sums; else they are merged before
+        L.part = take(plan.o ? chunk_bytes : std::max(chunk_bytes, sums));
+        L.gpart = plan.o ? take(sums) : L.part;
+    } else {
+        L.part = take(chunk_bytes);
     }
     L.table = take(k * (D / 2) * sizeof(float2));
     L.ints = take((4 * k + 1) * sizeof(int32_t));
@@ -182,8 +198,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                                                                (g->ctx_rows + ppk::kDecodeChunk - 1) / ppk::kDecodeChunk + k));
     const ppk::DecodeLayout Ly{k, chunks(g->max_len), chunks(g->n_new), n_ctx_items, g->ctx_off, g->ctx_span,
                                g->ctx_valid, g->pos0, g->gen_off};
-    const Mode mode = mode_of(cfg, g);
-    const bool split = mode != kWhole;
+    const Plan plan = plan_of(cfg, k);
     const int splits = tile_splits(k);
     float* gpart = reinterpret_cast<float*>(ws + L.gpart);
 
@@ -191,7 +206,7 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
     // norm adds them to x (pending = their split count) before normalising
     int pending = 0;
     auto norm = [&](const float* gain, void* out) {
-        if (split)
+        if (plan.split)
             ppk::residual_rmsnorm(x, gpart, pending, k, d, gain, out, eps, s);
         else
             ppk::rmsnorm(dt, x, gain, out, k, d, eps, s);
@@ -205,19 +220,19 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
         void* gk = static_cast<char*>(gen_k) + l * gen_layer;
         void* gv = static_cast<char*>(gen_v) + l * gen_layer;
         if (l > 0) norm(w->attn_norm[l], xn);
-        if (mode == kStream) {
+        if (bf) {
             const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
-            ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,
-                             ppk::DecodeEpi{nullptr, 0, qo}, s);
-            ppk::decode_attention(dt, q, hd, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, nullptr, hd, s);
-            const ppk::AttnChunks ac{part, g->ctx_span, step, Ly.n_ctx_chunks, Ly.n_ctx_chunks + Ly.n_gen_chunks, H};
-            ppk::decode_gemm_o(k, ac, w->wo[l], hd, d, hd, gpart, s);
-            pending = ppk::skinny_split(d, hd).splits;
-        } else if (bf) {
-            const ppk::QkvOut qo{q, hd, gk, gv, kvw, table, slot_pos, slot_kv, H, Hkv};
-            ppk::qkv_rope_bf16(xn, d, w->wqkv[l], d, k, d, nullptr, 0, qo, s);
-            ppk::decode_attention(dt, q, hd, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, attn, hd, s);
-            if (split) {
+            if (plan.paired)
+                ppk::decode_gemm(ppk::kQkvRope, xn, d, k, w->wqkv[l], d, qkv_w, d, gpart,
+                                 ppk::DecodeEpi{nullptr, 0, qo}, s);
+            else
+                ppk::qkv_rope_bf16(xn, d, w->wqkv[l], d, k, d, nullptr, 0, qo, s);
+            ppk::decode_attention(dt, q, hd, ck, cv, gk, gv, kvw, Ly, step, H, Hkv, D, part, plan.o ? nullptr : attn, hd, s);
+            if (plan.o) {
+                const ppk::AttnChunks ac{part, g->ctx_span, step, Ly.n_ctx_chunks, Ly.n_ctx_chunks + Ly.n_gen_chunks, H};
+                ppk::decode_gemm_o(k, ac, w->wo[l], hd, d, hd, gpart, s);
+                pending = ppk::skinny_split(d, hd).splits;
+            } else if (plan.split) {
                 ppk::gemm_partial_bf16(attn, hd, w->wo[l], hd, gpart, k, d, hd, splits, s);
                 pending = ppk::gemm_partial_splits(k, d, hd, splits);
             } else {
@@ -231,16 +246,16 @@ void enqueue_step(const pp_config* cfg, const pp_weights* w, const pp_gen_dlayou
                           hd, x, d, k, d, hd, s);
         }
         norm(w->mlp_norm[l], xn);
-        if (mode == kStream) {
-            const ppk::QkvOut none{};
-            ppk::decode_gemm(ppk::kSwiGLU, xn, d, k, w->w_gateup[l], d, 2 * F, d, gpart,
-                             ppk::DecodeEpi{act, F, none}, s);
-            ppk::decode_gemm(ppk::kResidual, act, F, k, w->w_down[l], F, d, F, gpart,
-                             ppk::DecodeEpi{x, d, none}, s);
-            pending = ppk::decode_gemm_splits(k, d, F);
-        } else if (bf) {
-            ppk::gemm_bf16(ppk::kSwiGLU, xn, d, w->w_gateup[l], d, act, F, k, 2 * F, d, nullptr, 0, s);
-            if (split) {
+        if (bf) {
+            if (plan.paired)
+                ppk::decode_gemm(ppk::kSwiGLU, xn, d, k, w->w_gateup[l], d, 2 * F, d, gpart,
+                                 ppk::DecodeEpi{act, F, ppk::QkvOut{}}, s);
+            else
+                ppk::gemm_bf16(ppk::kSwiGLU, xn, d, w->w_gateup[l], d, act, F, k, 2 * F, d, nullptr, 0, s);
+            if (plan.down) {
+                ppk::decode_gemm(ppk::kResidual, act, F, k, w->w_down[l], F, d, F, gpart, ppk::DecodeEpi{}, s);
+                pending = ppk::decode_gemm_splits(k, d, F);
+            } else if (plan.split) {
                 ppk::gemm_partial_bf16(act, F, w->w_down[l], F, gpart, k, d, F, splits, s);
                 pending = ppk::gemm_partial_splits(k, d, F, splits);
             } else {

@@ -13,14 +13,14 @@
 //                        do not merge them in the O projection's staging, below).
 // The projections of a step of up to 16 prompts (more take the prefill's GEMM tiles): C[k, N] =
 // A[k, K] W[N, K]^T is bound by streaming W from HBM.
-// rowpair_seg_kernel     QKV and gate/up at K = 2048 or 4096: one workgroup per 32 weight
+// rowpair_seg_kernel     QKV and gate/up at K = 256, 512, 1024, 2048 or 4096: one workgroup per 32 weight
 //                        rows whose epilogue belongs together (rotate-half pairs; gate and up
 //                        rows of the same features), the weights loaded as whole 1 KB row
 //                        segments straight into an LDS ring, K split four ways across the
 //                        wavefronts and added through LDS; RoPE with the query store and the
 //                        key/value append, or SwiGLU, in the same kernel.
 // qkv_seg16_kernel       QKV in that style with 16 rows per workgroup (8 dims and their
-//                        rotate-half partners) when the 32-row groups outnumber the CUs.
+//                        rotate-half partners) at K = 2048 or 4096 when the 32-row groups outnumber the CUs.
 // splitk_seg_kernel      down (N = d) in that style: 32 rows x a K split per workgroup, float32
 //                        partial sums per split.
 // o_proj_kernel          O (N = d): about 512 pieces of 64 rows x a K split of up to 6 tiles of
@@ -643,7 +643,7 @@ __device__ __forceinline__ int rs_swz(int r) { return (r & 1) | (((r >> 1) & 1) 
 
 template <int EPI, int NSEG, int NW>
 __global__ __launch_bounds__(256, 2) void rowpair_seg_kernel(const bf16* __restrict__ A, int64_t lda, int k,
-                                                             const bf16* __restrict__ W, int64_t ldw,
+                                                             const bf16* __restrict__ W, int64_t ldw, int K,
                                                              ppk::DecodeEpi ep) {
     static_assert(NW >= 2 && NW * RS_CHUNK_B >= 4 * 2 * 64 * 16, "ring, and room for the reduction");
     constexpr int NCH = 2 * NSEG;               // chunks: segment-major, block nb within a segment
@@ -665,8 +665,11 @@ __global__ __launch_bounds__(256, 2) void rowpair_seg_kernel(const bf16* __restr
     const int rot = (g >> 3) & (NSEG - 1);
     // one descriptor over rows r0[0] .. r0[1] + 15 (80 rows at most)
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16*>(W + int64_t(r0[0]) * ldw), 0, static_cast<int>((int64_t(r0[1] - r0[0] + 15) * ldw + RS_COLS * NSEG) * 2),
-        kRsrcWord3);
+        const_cast<bf16*>(W + int64_t(r0[0]) * ldw), 0, static_cast<int>((int64_t(r0[1] - r0[0] + 15) * ldw + K) * 2), kRsrcWord3);
+    // K of half a segment: the pieces past it read pieces inside it, for the wavefronts of those
+    // columns, which add nothing
+    const int qv = NSEG == 1 ? K / 8 : 64;
+    const bool mine = NSEG > 1 || 128 * w < K;
     auto issue = [&](int c) {                   // chunk c (clamped) into slot c % NW
         const int cc = c < NCH ? c : NCH - 1, sg = cc >> 1, nb = cc & 1;
         char* slot = smem + (c % NW) * RS_CHUNK_B;
@@ -675,7 +678,8 @@ __global__ __launch_bounds__(256, 2) void rowpair_seg_kernel(const bf16* __restr
             const int r = 4 * w + t;
             const int soff =
                 static_cast<int>((int64_t(r0[nb] - r0[0] + r) * ldw + ((sg + rot) & (NSEG - 1)) * RS_COLS) * 2);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void*)(slot + r * 1024), 16, 16 * (lane ^ rs_swz(r)),
+            const int q = lane ^ rs_swz(r);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void*)(slot + r * 1024), 16, 16 * (q < qv ? q : q & 15),
                                                      soff, 0, 0);
         }
     };
@@ -686,7 +690,7 @@ __global__ __launch_bounds__(256, 2) void rowpair_seg_kernel(const bf16* __restr
 #pragma unroll
     for (int c = 0; c < NW - 1; ++c) issue(c);
     __builtin_amdgcn_sched_barrier(0);
-    const bf16* arow = A + int64_t(min(lr, k - 1)) * lda + 128 * w + 8 * q4;
+    const bf16* arow = A + int64_t(min(lr, k - 1)) * lda + (mine ? 128 * w : 0) + 8 * q4;
     bf16x8 pf[NSEG][4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) pf[0][st] = *reinterpret_cast<const bf16x8*>(arow + rot * RS_COLS + 32 * st);
@@ -708,6 +712,7 @@ __global__ __launch_bounds__(256, 2) void rowpair_seg_kernel(const bf16* __restr
                 pf[sg + 1][st] =
                     *reinterpret_cast<const bf16x8*>(arow + ((sg + 1 + rot) & (NSEG - 1)) * RS_COLS + 32 * st);
         }
+        if (!mine) continue;
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
             const bf16x8 wf = *reinterpret_cast<const bf16x8*>(slot + lr * 1024 +
@@ -835,7 +840,7 @@ void launch_qkv_seg16(int N, hipStream_t s, const bf16* A, int64_t lda, int k, c
 }
 
 template <int EPI, int NSEG, int NW>
-void launch_rowpair_seg(int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
+void launch_rowpair_seg(int N, int K, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
                         const ppk::DecodeEpi& ep) {
     constexpr int lds = NW * RS_CHUNK_B;
     static bool attr = [] {
@@ -844,28 +849,30 @@ void launch_rowpair_seg(int N, hipStream_t s, const bf16* A, int64_t lda, int k,
         return true;
     }();
     (void)attr;
-    rowpair_seg_kernel<EPI, NSEG, NW><<<N / 32, 256, lds, s>>>(A, lda, k, W, ldw, ep);
+    rowpair_seg_kernel<EPI, NSEG, NW><<<N / 32, 256, lds, s>>>(A, lda, k, W, ldw, K, ep);
 }
 
 // rowpair_seg_kernel's ring depth follows the grid: three workgroups of 48 KB per CU when there
 // are more than 512 of them, else two of 64 KB.
 template <int EPI, int NSEG>
-void launch_rowpair(int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
+void launch_rowpair(int N, int K, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
                     const ppk::DecodeEpi& ep) {
-    if (N / 32 > 512) launch_rowpair_seg<EPI, NSEG, 3>(N, s, A, lda, k, W, ldw, ep);
-    else launch_rowpair_seg<EPI, NSEG, 4>(N, s, A, lda, k, W, ldw, ep);
+    if (N / 32 > 512) launch_rowpair_seg<EPI, NSEG, 3>(N, K, s, A, lda, k, W, ldw, ep);
+    else launch_rowpair_seg<EPI, NSEG, 4>(N, K, s, A, lda, k, W, ldw, ep);
 }
 
-// QKV and gate/up at K = 512 NSEG.
+// QKV and gate/up at K = 512 NSEG (256 too for NSEG = 1).
 template <int NSEG>
-void launch_paired(int epi, int N, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
+void launch_paired(int epi, int N, int K, hipStream_t s, const bf16* A, int64_t lda, int k, const bf16* W, int64_t ldw,
                    const ppk::DecodeEpi& ep) {
     // QKV: 16-row workgroups when the 32-row groups outnumber the CUs (7B: 384 groups become 768
     // workgroups, 21.4 -> 20.5 us); with fewer groups (Mistral-7B and 1.3B: 192) the 32-row
     // kernel is faster (16 rows: 2.6% and 3.7% slower steps)
-    if (epi == ppk::kSwiGLU) launch_rowpair<ppk::kSwiGLU, NSEG>(N, s, A, lda, k, W, ldw, ep);
-    else if (N / 32 > 256) launch_qkv_seg16<NSEG, 3>(N, s, A, lda, k, W, ldw, ep.qkv);
-    else launch_rowpair<ppk::kQkvRope, NSEG>(N, s, A, lda, k, W, ldw, ep);
+    if (epi == ppk::kSwiGLU) return launch_rowpair<ppk::kSwiGLU, NSEG>(N, K, s, A, lda, k, W, ldw, ep);
+    if constexpr (NSEG >= 4) {
+        if (N / 32 > 256) return launch_qkv_seg16<NSEG, 3>(N, s, A, lda, k, W, ldw, ep.qkv);
+    }
+    launch_rowpair<ppk::kQkvRope, NSEG>(N, K, s, A, lda, k, W, ldw, ep);
 }
 
 // Split-K projection for up to 16 prompts (the down projection, whose N = d leaves too few
@@ -1142,9 +1149,7 @@ int decode_gemm_splits(int k, int N, int K) {
     return ss.s ? ss.splits : skinny_split(N, K).splits;
 }
 
-bool decode_stream_ok(int k, int d, int hd, int F) {
-    return k >= 1 && k <= 16 && (d == 2048 || d == 4096) && hd % SG_TILE == 0 && F % 128 == 0;
-}
+bool decode_paired_ok(int K) { return K == 256 || K == 512 || K == 1024 || K == 2048 || K == 4096; }
 
 void residual_rmsnorm(float* x, const float* part, int S, int k, int d, const float* g, void* out, float eps,
                       hipStream_t s) {
@@ -1162,9 +1167,12 @@ void decode_gemm(int epi, const void* A, int64_t lda, int k, const void* W, int6
     const bf16* a = static_cast<const bf16*>(A);
     const bf16* w = static_cast<const bf16*>(W);
     if (epi != kResidual) {
-        if (K == 4096) launch_paired<8>(epi, N, s, a, lda, k, w, ldw, ep);
-        else launch_paired<4>(epi, N, s, a, lda, k, w, ldw, ep);   // 2048
-        return;
+        switch (K) {
+            case 4096: return launch_paired<8>(epi, N, K, s, a, lda, k, w, ldw, ep);
+            case 2048: return launch_paired<4>(epi, N, K, s, a, lda, k, w, ldw, ep);
+            case 1024: return launch_paired<2>(epi, N, K, s, a, lda, k, w, ldw, ep);
+            default: return launch_paired<1>(epi, N, K, s, a, lda, k, w, ldw, ep);   // 512, 256
+        }
     }
     // split-K partial sums, added to the residual stream by residual_rmsnorm
     const SegSplit ss = seg_split(k, N, K);

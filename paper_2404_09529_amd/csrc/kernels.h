@@ -166,9 +166,8 @@ struct SkinnySplit {
     int tiles_per_split, splits;
 };
 SkinnySplit skinny_split(int N, int K);
-// Shapes decode_gemm and decode_gemm_o take (bf16, head dim 128): up to 16 prompts at widths d of
-// 2048 or 4096, the query width hd = H D and F multiples of 128.
-bool decode_stream_ok(int k, int d, int hd, int F);
+// Widths K at which decode_gemm takes QKV and gate/up.
+bool decode_paired_ok(int K);
 
 // The O projection of a decode step (bf16, head dim 128, k <= 16): its activations are the
 // attention output, merged from the attention's chunk results while they are staged; float32
@@ -184,7 +183,7 @@ void residual_rmsnorm(float* x, const float* part, int S, int k, int d, const fl
 bool residual_rmsnorm_ok(int d);
 
 // bf16 C = A W^T for k <= 16 rows (A [k, lda], W [N, ldw]) with the epilogue `epi`:
-// kSwiGLU and kQkvRope in the GEMM kernel itself (N % 32 == 0; K 2048 or 4096); kResidual
+// kSwiGLU and kQkvRope in the GEMM kernel itself (N % 32 == 0; decode_paired_ok(K)); kResidual
 // leaves float32 partial sums in part (decode_gemm_splits(k, N, K) * k * N floats) for
 // residual_rmsnorm to add.
 void decode_gemm(int epi, const void* A, int64_t lda, int k, const void* W, int64_t ldw, int N, int K, float* part,

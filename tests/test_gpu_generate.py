@@ -193,6 +193,22 @@ def _teacher_forced(model_name, lengths, n_layers, n_new, picks):
 
 
 # ----------------------------------------------------------------------------- layouts and entry points agree
+@pytest.mark.parametrize("dims,lengths", [
+    (dict(d_model=256, n_heads=2, n_kv_heads=2, ffn_dim=384), [5, 1, 300]),         # half a segment; a tail of 384
+    (dict(d_model=512, n_heads=4, n_kv_heads=2, ffn_dim=768), [9] * 15 + [140]),    # one segment
+    (dict(d_model=1024, n_heads=4, n_kv_heads=4, ffn_dim=1280), [9, 130, 1]),       # two
+    (dict(d_model=768, n_heads=6, n_kv_heads=6, ffn_dim=896), [9, 130, 1]),         # O and down streamed only
+    (dict(d_model=6144, n_heads=4, n_kv_heads=4, ffn_dim=640), [9, 130, 1, 4, 2]),  # O at its last prompt count there
+    (dict(d_model=6144, n_heads=4, n_kv_heads=4, ffn_dim=640), [9, 130, 1, 4, 2, 3]),   # down only
+    (dict(d_model=7168, n_heads=4, n_kv_heads=4, ffn_dim=640), [9, 130]),           # tiles only
+])
+def test_bf16_decode_steps_of_few_prompts(dims, lengths):
+    """Up to 16 prompts: every choice between the streaming kernels and the tiles, two layers."""
+    name = f"d{dims['d_model']}s"
+    WIDE[name] = dims
+    _teacher_forced(name, lengths, 2, 2, sorted({0, 1, 2, len(lengths) - 1} & set(range(len(lengths)))))
+
+
 @pytest.mark.parametrize("model_name,lengths,n_layers,n_new", [
     ("llama2-7b", [3] * 16 + [150], 1, 2),                            # 17 prompts: the first count on the tiles
     ("d1024", [9, 130, 1], 2, 3),
