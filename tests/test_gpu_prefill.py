@@ -82,6 +82,18 @@ def test_fp32_fused_qkv_head_sizes(H, Hkv, Dh):
         assert np.array_equal(a, b)
 
 
+def test_fp32_packed_equals_padded_where_their_tiles_differ():
+    """d 64: the padded batch's projections have tiles enough for a wavefront each, the packed one's not."""
+    case = W.make_case(1, 5, lengths=np.array([700, 3, 40, 1, 2]), capacity=760, random_gains=True, n_layers=2, d_model=64,
+                       n_heads=4, n_kv_heads=4, head_dim=64, ffn_dim=304)
+    packed = gpu_prefill(case, pp.pp_pack(case.lengths, case.capacity))
+    padded = gpu_prefill(case, pp.pp_pack_padded(case.lengths))
+    for mx, mean in _check_bar("f32 d64", packed, _oracle(case), 2):
+        assert mx <= 1e-4 and mean <= 1e-5
+    for a, b in zip([packed[0], *packed[1], *packed[2]], [padded[0], *padded[1], *padded[2]]):
+        assert np.array_equal(a, b)
+
+
 # d below, at and past the row lengths that the first launch holds in registers
 @pytest.mark.parametrize("H,Hkv,Dh,d", [(4, 4, 64, 256), (2, 1, 128, 256), (4, 2, 64, 80), (2, 1, 64, 272), (1, 1, 64, 1040),
                                         (1, 1, 64, 8208)])

@@ -209,6 +209,26 @@ def test_gemm_f32_tiles(M, N, K, ldc, epi):
     assert np.array_equal(got[:M, N:], C0[:M, N:]) and np.array_equal(got[M], C0[M])
 
 
+@pytest.mark.parametrize("M,N,K,ldc", [(545, 2070, 16, 2070), (600, 2048, 32, 2052), (577, 2049, 48, 2049), (1100, 1024, 64, 1024),
+                                       (600, 2048, 80, 2048), (70, 512, 240, 512)])
+@pytest.mark.parametrize("epi", [pp.PP_EPI_STORE, pp.PP_EPI_RESIDUAL])
+def test_gemm_f32_short_k(M, N, K, ldc, epi):
+    """K of few steps: many tiles (a wavefront each up to K = 64), an odd count of them, against float64
+    and bit for bit against the same rows in a call of few tiles."""
+    rng = np.random.default_rng([M, N, K])
+    A = f32_dev(rng.standard_normal((M, K)))
+    B = f32_dev(rng.standard_normal((N, K)) * 0.02)
+    C0 = f32_dev(rng.standard_normal((M + 1, ldc)))
+    got, few = C0.clone(), C0.clone()
+    pp.pp_gemm(pp.PP_F32, epi, A, K, B, K, got, ldc, M, N, K)
+    pp.pp_gemm(pp.PP_F32, epi, A, K, B, K, few, ldc, 33, N, K)
+    assert torch.equal(got[:33], few[:33])
+    assert torch.equal(got[M:], C0[M:]) and torch.equal(got[:, N:], C0[:, N:]) and torch.equal(few[33:], C0[33:])
+    want = A.double() @ B.double().t().contiguous() + (C0[:M, :N].double() if epi == pp.PP_EPI_RESIDUAL else 0)
+    # float32 sums of K products of about 0.02: K 2^-24 sum |a b| and the rounding of a result of up to 5
+    assert float((got[:M, :N].double() - want).abs().max()) <= 1e-5
+
+
 # ----------------------------------------------------------------------------- attention
 ATTN_CASES = [
     # lengths, capacity, H, Hkv  (segments shorter / longer than a tile, ragged tails, rows with pads)
