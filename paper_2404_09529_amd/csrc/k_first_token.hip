@@ -431,31 +431,34 @@ __global__ __launch_bounds__(256, 1) void lm_head_seg_kernel(const bf16* __restr
 }
 
 // float32 model: one wavefront per vocabulary row, four rows per workgroup (its lanes split d,
-// the row read once, coalesced), prompts in groups of 8 so that their sums and reductions across
-// the wavefront overlap (one prompt at a time, 8 prompts at vocabulary 1000: 12 us; now 5).
+// the row read once, coalesced), prompts in groups of G = 1, 2, 4 or 8 so that their sums and
+// reductions across the wavefront overlap (one prompt at a time, 8 prompts at vocabulary 1000: 12
+// us; now 5).  The group is no larger than the prompts need: with 8, one prompt's sums were formed
+// eight times (vocabulary 32000, d 4096, the whole call for 1 prompt: 308 us, 224 with 1; for 4: 310, 231).
+template <int G>
 __global__ __launch_bounds__(256) void lm_head_f32_kernel(const float* __restrict__ hl, int k, const float* __restrict__ W,
                                                           int V, int d, float* __restrict__ logits,
                                                           ArgMax* __restrict__ part) {
     const int n = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (n >= V) return;
     const float* w = W + int64_t(n) * d;
-    for (int m0 = 0; m0 < k; m0 += 8) {
-        const float* h[8];
-        float s[8];
+    for (int m0 = 0; m0 < k; m0 += G) {
+        const float* h[G];
+        float s[G];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < G; ++u) {
             h[u] = hl + int64_t(min(m0 + u, k - 1)) * d;
             s[u] = 0.f;
         }
         for (int c = lane; c < d; c += 64) {
             const float wc = w[c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s[u] = fmaf(h[u][c], wc, s[u]);
+            for (int u = 0; u < G; ++u) s[u] = fmaf(h[u][c], wc, s[u]);
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = wave_sum(s[u]);
+        for (int u = 0; u < G; ++u) s[u] = wave_sum(s[u]);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < G; ++u) {
             if (lane != u || m0 + u >= k) continue;
             if (logits) logits[int64_t(m0 + u) * V + n] = s[u];
             part[int64_t(m0 + u) * V + n] = ArgMax{s[u], n};   // a NaN logit never wins the final reduction
@@ -590,7 +593,12 @@ void next_token(int dtype, int k, const void* lm_head, int V, int d, void* works
             lm_head_tiles(hl, k, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
     } else {
         const float* hl = reinterpret_cast<const float*>(ws);
-        lm_head_f32_kernel<<<(V + 3) / 4, 256, 0, s>>>(hl, k, static_cast<const float*>(lm_head), V, d, logits, part);
+        const float* W = static_cast<const float*>(lm_head);
+        const unsigned blocks = (V + 3) / 4;
+        if (k == 1) lm_head_f32_kernel<1><<<blocks, 256, 0, s>>>(hl, k, W, V, d, logits, part);
+        else if (k == 2) lm_head_f32_kernel<2><<<blocks, 256, 0, s>>>(hl, k, W, V, d, logits, part);
+        else if (k <= 4) lm_head_f32_kernel<4><<<blocks, 256, 0, s>>>(hl, k, W, V, d, logits, part);
+        else lm_head_f32_kernel<8><<<blocks, 256, 0, s>>>(hl, k, W, V, d, logits, part);
     }
     argmax_finalize_kernel<<<k, 256, 0, s>>>(part, n_blocks, k, tokens);
 }

@@ -30,7 +30,7 @@ def _cfg(d, V, dtype=pp.PP_BF16):
     if dtype == pp.PP_BF16:
         return pp.PPConfig(n_layers=1, d_model=d, n_heads=d // 128, n_kv_heads=d // 128, head_dim=128,
                            ffn_dim=4 * d, vocab=V, dtype=dtype, rms_eps=1e-5, rope_theta=1e4)
-    return pp.PPConfig(n_layers=1, d_model=d, n_heads=d // 64, n_kv_heads=d // 64, head_dim=64, ffn_dim=4 * d,
+    return pp.PPConfig(n_layers=1, d_model=d, n_heads=max(d // 64, 1), n_kv_heads=max(d // 64, 1), head_dim=64, ffn_dim=4 * d,
                        vocab=V, dtype=dtype, rms_eps=1e-5, rope_theta=1e4)
 
 
@@ -156,6 +156,17 @@ def test_first_token_f32():
     lengths = [6, 1, 11, 4]
     d, V = 64, 50
     hidden = rng.standard_normal((22, d)).astype(np.float32)
+    lm_head = (0.02 * rng.standard_normal((V, d))).astype(np.float32)
+    tokens, logits = _run(lengths, hidden, lm_head, dtype=pp.PP_F32)
+    _check(lengths, hidden, lm_head, tokens, logits, bf16=False)
+
+
+@pytest.mark.parametrize("k,V,d", [(1, 1, 16), (1, 1003, 144), (2, 50, 80), (3, 129, 256), (5, 34, 64), (9, 257, 272)])
+def test_first_token_f32_prompt_groups(k, V, d):
+    """Prompt counts below, at and past the groups of 1, 2, 4 and 8; rows that are no whole wavefront."""
+    rng = np.random.default_rng([k, V, d])
+    lengths = list(rng.integers(1, 5, k))
+    hidden = rng.standard_normal((int(np.sum(lengths)), d)).astype(np.float32)
     lm_head = (0.02 * rng.standard_normal((V, d))).astype(np.float32)
     tokens, logits = _run(lengths, hidden, lm_head, dtype=pp.PP_F32)
     _check(lengths, hidden, lm_head, tokens, logits, bf16=False)
