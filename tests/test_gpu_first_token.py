@@ -161,7 +161,7 @@ def test_first_token_f32():
     _check(lengths, hidden, lm_head, tokens, logits, bf16=False)
 
 
-@pytest.mark.parametrize("k,V,d", [(1, 1, 16), (1, 1003, 144), (2, 50, 80), (3, 129, 256), (5, 34, 64), (9, 257, 272)])
+@pytest.mark.parametrize("k,V,d", [(1, 2, 16), (1, 1003, 144), (2, 50, 80), (3, 129, 256), (5, 34, 64), (9, 257, 272)])
 def test_first_token_f32_prompt_groups(k, V, d):
     """Prompt counts below, at and past the groups of 1, 2, 4 and 8; rows that are no whole wavefront."""
     rng = np.random.default_rng([k, V, d])
