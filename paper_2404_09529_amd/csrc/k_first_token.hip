@@ -549,6 +549,24 @@ hipError_t first_token_scratch(void** ptr) {
     return hipSuccess;
 }
 
+namespace {
+
+// More than 64 prompts: as a projection on 128-prompt x 256-row tiles, whose fragment reads and loads
+// overlap the MFMAs, or on 128 vocabulary rows a workgroup, twice as many of them.  The tiles: where
+// one pass of 128 prompts is not enough (d 4096, the whole call: 200 prompts, vocabulary 128256, 484 -> 324
+// us; 140, vocabulary 32000, 116 -> 92); else where they give every CU one (96 prompts, vocabulary 32000:
+// 76 us, 87 on the tiles) and, up to 96 prompts, the CUs' rounds of tiles, each of about 5/3 the time of
+// a round of workgroups, are the shorter ones: 66 prompts, vocabulary 65536 (one round; two of workgroups)
+// 186 -> 182, 66000 (two; three) 225 and 235, 100000 (two; four) 283 -> 227; 96 prompts, d 2048, 151936 (three;
+// five) 239 -> 225; 128 prompts, 66000, 239 and 243 at d 4096, 98 -> 92 at d 1024.
+bool lm_head_on_tiles(int k_pad, int V) {
+    const int cu = cu_count(), tiles = (V + 255) / 256, blocks = (V + LM_ROWS - 1) / LM_ROWS;
+    if (k_pad > 128) return true;
+    return tiles >= cu && (k_pad > 96 || 5 * ((tiles + cu - 1) / cu) <= 3 * ((blocks + cu - 1) / cu));
+}
+
+}  // namespace
+
 size_t first_token_workspace(int dtype, int k, int V, int d) {
     const int k_pad = (k + 15) / 16 * 16;
     const size_t e = dtype == PP_BF16 ? 2 : 4;
@@ -582,15 +600,10 @@ void next_token(int dtype, int k, const void* lm_head, int V, int d, void* works
             lm_head_seg_launch<4>(hl, k, k_pad, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
         else if (k_pad <= 64)
             lm_head_launch<4, 64, 4, 2>(hl, k, k_pad, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
-        // More than 64 prompts: as a projection on 128-prompt x 256-row tiles, whose fragment reads and
-        // loads overlap the MFMAs, where those give every CU a tile or one pass is not enough (d 4096:
-        // 128 prompts, vocabulary 128256, 292 -> 242 us for the whole call; 200 prompts 484 -> 324; 140
-        // prompts, vocabulary 32000, 116 -> 92); else on 128 vocabulary rows a workgroup, twice as
-        // many of them (96 prompts, vocabulary 32000: 76 us, 87 on the tiles)
-        else if (k_pad <= 128 && (V + 255) / 256 < cu_count())
-            lm_head_launch<8, 64, 4, 2>(hl, k, k_pad, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
-        else
+        else if (lm_head_on_tiles(k_pad, V))
             lm_head_tiles(hl, k, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
+        else
+            lm_head_launch<8, 64, 4, 2>(hl, k, k_pad, static_cast<const bf16*>(lm_head), V, d, logits, part, n_blocks, s);
     } else {
         const float* hl = reinterpret_cast<const float*>(ws);
         const float* W = static_cast<const float*>(lm_head);

@@ -128,10 +128,14 @@ def test_first_token_ties_go_to_the_lowest_id_and_nan_gives_minus_one(d):
 
 
 @pytest.mark.parametrize("k,V,d", [(65, 2, 256), (128, 127, 256), (129, 257, 512), (70, 385, 2048), (257, 1003, 256),
-                                   (66, 65537, 256)])
+                                   (66, 65537, 256),
+                                   # past one pass of 128 prompts: the tiles at any vocabulary
+                                   (130, 2, 256), (200, 127, 512), (140, 385, 2048),
+                                   # one pass: both sides of the choice by rounds of the CUs
+                                   (66, 65536, 256), (96, 65793, 256), (97, 65793, 256), (66, 98305, 256)])
 def test_first_token_bf16_tiles(k, V, d):
-    """More than 64 prompts: vocabularies around the 128- and 256-row blocks of a tile, odd ones,
-    prompt counts around its 128 rows; ties and an all-NaN row; with and without logits."""
+    """More than 64 prompts, on the tiles or 128 vocabulary rows a workgroup: vocabularies around the 128- and
+    256-row blocks of a tile, odd ones, prompt counts around its 128 rows; ties and an all-NaN row; with and without logits."""
     rng = np.random.default_rng([k, V, d])
     lengths = list(rng.integers(1, 4, k))
     hidden = rng.standard_normal((int(np.sum(lengths)), d)).astype(np.float32)
