@@ -622,8 +622,10 @@ void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
 // on tile size `tile` of gemm_tiles.
 //
 // The estimate: a kernel's time is the tiles of its busiest CU, each K / 64 steps of a measured
-// length (kBigStep, kTileStep; they hold within 10% over K 2048 .. 14336 and from one tile per CU
-// to twenty), and about 4 us for a launch.  The 256 x 256 tile has the best rate (1.34 us a step,
+// length (kBigStep, kTileStep, taken with the weights in L2 or the Infinity Cache; K 2048 .. 14336), and
+// about 4 us for a launch.  It ranks tiles; it knows no HBM: weights read from there for one or two
+// row tiles take longer (48 rows, gate/up at N 28672, K 4096: 33 us estimated, 52 measured; QKV 15.5 and 19.2;
+// 1309 rows, N 11008, K 2048: 47 and 54; N 2048, K 5504: 51 and 59).  The 256 x 256 tile has the best rate (1.34 us a step,
 // 1600 TFLOP/s on all CUs) but few rows make few tiles: at 344 rows N = 2048, K = 5504 gives it 16
 // tiles, 109 us, and 64 x 64 gives 192, 25 us.  One more M-tile than fills whole rounds costs a
 // round: the rows past the whole rounds then go to smaller tiles (2926 rows, N = 6144, K = 4096:
@@ -632,7 +634,12 @@ void launch(const GemmArgs& g, int n_mt, hipStream_t s) {
 // 2% (27,721 rows, N = 12288) measured as nothing.  Rows that make three quarters of a round make a
 // whole one of 192-row tiles at 1.10 us a step (2926 rows, N = 4096: 192 tiles of 256 rows, O 107 and
 // down 320 us; 256 of 192 rows, 90 and 274 us).
+// The plain store also writes its bf16 values at 3.9 TB/s as whole rows from LDS (this kernel) and 2.8
+// straight from the registers (the small tiles), every CU's at about the same time: at a short K that
+// decides (2100 rows, N 22016, K 512: 67 us, 80 on small tiles).  The stores of a split's
+// two launches get in each other's way: about 4.5 us.
 constexpr float kBigStep = 1.34f, kStep192 = 1.10f, kLaunch = 4.0f;
+constexpr float kStoreBig = 2 / 3.9e6f, kStoreTile = 2 / 2.8e6f, kStoreWait = 4.5f;   // us per element; us
 
 struct GemmSplit {
     int big, tile;   // big < 0: every row on 192-row tiles
@@ -640,8 +647,10 @@ struct GemmSplit {
 GemmSplit gemm_split(int epi, int n_mt, int M, int N, int K, bool list) {
     const int tiles_n = N / BN, wg = cu_count() / 8;
     const float steps = static_cast<float>(K / BK);
+    // of a row of the plain store
+    const float store_big = epi == kStore ? N * kStoreBig : 0.f, store_tile = epi == kStore ? N * kStoreTile : 0.f;
     auto big_time = [&](int n) {
-        return n ? kLaunch + steps * kBigStep * ceil_div(xcd_split(n, tiles_n, wg).tiles, wg) : 0.f;
+        return n ? kLaunch + steps * kBigStep * ceil_div(xcd_split(n, tiles_n, wg).tiles, wg) + min(n * BM, M) * store_big : 0.f;
     };
     GemmSplit best{n_mt, 0};
     float best_time = big_time(n_mt);
@@ -651,7 +660,8 @@ GemmSplit gemm_split(int epi, int n_mt, int M, int N, int K, bool list) {
         const int last = list && n_mt == ceil_div(M, BM) ? n_mt * BM - M : 0;   // rows the last tile lacks
         for (int t = 0; t < kGemmTiles; ++t) {
             const int tiles = ceil_div(rows - last, kTileRows[t]) * (N / kTileCols[t]);
-            const float time = big_time(big) + kLaunch + steps * kTileStep[t] * ceil_div(ceil_div(tiles, 8), wg);
+            const float time = big_time(big) + kLaunch + steps * kTileStep[t] * ceil_div(ceil_div(tiles, 8), wg) +
+                               (rows - last) * store_tile + (big && epi == kStore ? kStoreWait : 0.f);
             if (time < best_time * (big ? 0.95f : 1.f)) {
                 best_time = time;
                 best = GemmSplit{big, t};
