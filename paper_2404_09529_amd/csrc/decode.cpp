@@ -32,7 +32,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 size_t elem_size(int dtype) { return dtype == PP_BF16 ? 2 : 4; }
 
 struct Layout {
-    size_t x = 0, xn = 0, q = 0, attn = 0, act = 0, h = 0, part = 0, table = 0, ints = 0, ft = 0, gpart = 0,
+    size_t x = 0, xn = 0, q = 0, attn = 0, act = 0, part = 0, table = 0, ints = 0, ft = 0, gpart = 0,
            total = 0;
 };
 
@@ -108,7 +108,6 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.q = take(c->dtype == PP_BF16 ? k * hd * 2 : k * qkv_w * 4);   // bf16: rotated queries only
     L.attn = take(k * hd * e);
     L.act = take(k * F * e);
-    L.h = take(k * d * 4);   // no longer used; the documented size of a workspace holds it
     const size_t chunk_bytes = k * size_t(c->n_heads) * nch * (D + 4) * 4;
     const Plan plan = plan_of(c, g->k);
     if (plan.split) {
@@ -125,7 +124,7 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
         L.part = take(chunk_bytes);
     }
     L.table = take(k * (D / 2) * sizeof(float2));
-    L.ints = take((4 * k + 1) * sizeof(int32_t));
+    L.ints = take(2 * k * sizeof(int32_t));
     L.ft = take(ppk::first_token_workspace(c->dtype, g->k, c->vocab, c->d_model));
     L.total = off;
     return L;

@@ -51,32 +51,6 @@ constexpr int CH = ppk::kDecodeChunk;   // keys per chunk: 4 wavefronts x IT ite
 constexpr int IT = CH / 32;
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <typename T, int DL>
-__device__ __forceinline__ void load_slice(const T* p, float* v) {
-#pragma unroll
-    for (int e = 0; e < DL; e += 8) load8(p + e, v + e);
-}
-
-// A slice of DL elements held as 16-byte pieces -> float.
-template <typename T, int DL>
-__device__ __forceinline__ void unpack_slice(const u32x4* raw, float* v) {
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-        for (int c = 0; c < DL / 8; ++c) {
-            const bf16x8 b = __builtin_bit_cast(bf16x8, raw[c]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[8 * c + e] = static_cast<float>(b[e]);
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < DL / 4; ++c) {
-            const f32x4 f = __builtin_bit_cast(f32x4, raw[c]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * c + e] = f[e];
-        }
-    }
-}
-
 // (m, l, o) <- merge of two partial softmax results over disjoint key sets (base-2 scores).
 template <int DL>
 __device__ __forceinline__ void merge(float& m, float& l, float* o, float m2, float l2, const float* o2) {
@@ -93,10 +67,10 @@ __device__ __forceinline__ void merge(float& m, float& l, float* o, float m2, fl
 // output) for the group's R query heads into part.  The float32 form: lane l of wavefront w has key
 // group kg = l / 8 (one key per iteration) and dimension slice dl = l % 8 (D / 8 consecutive
 // elements); keys of the chunk: j0 + 8 IT w + 8 it + kg.
-template <typename T, int D, int R>
-__device__ __forceinline__ void decode_attn_chunk(
-    const T* __restrict__ q, int64_t ldq, const T* __restrict__ ctx_k, const T* __restrict__ ctx_v,
-    const T* __restrict__ gen_k, const T* __restrict__ gen_v, int64_t ldkv, const int32_t* __restrict__ ctx_off,
+template <int D, int R>
+__device__ __forceinline__ void decode_attn_chunk_f32(
+    const float* __restrict__ q, int64_t ldq, const float* __restrict__ ctx_k, const float* __restrict__ ctx_v,
+    const float* __restrict__ gen_k, const float* __restrict__ gen_v, int64_t ldkv, const int32_t* __restrict__ ctx_off,
     const int32_t* __restrict__ ctx_span, const int32_t* __restrict__ ctx_valid, const int32_t* __restrict__ gen_off,
     int step, int Hkv, int n_ctx_chunks, int n_chunks, float* __restrict__ part, int i, int g, int c) {
     constexpr int DL = D / 8;
@@ -104,8 +78,8 @@ __device__ __forceinline__ void decode_attn_chunk(
     __shared__ float red[4][R][D + 2];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int kg = lane >> 3, dl = lane & 7;
-    const T* K;
-    const T* V;
+    const float* K;
+    const float* V;
     int64_t row0;
     int j0, jend, valid;
     if (c < n_ctx_chunks) {
@@ -130,7 +104,8 @@ __device__ __forceinline__ void decode_attn_chunk(
     float qf[R][DL];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        load_slice<T, DL>(q + int64_t(i) * ldq + int64_t(g * R + r) * D + dl * DL, qf[r]);
+#pragma unroll
+        for (int e = 0; e < DL; e += 8) load8(q + int64_t(i) * ldq + int64_t(g * R + r) * D + dl * DL + e, qf[r] + e);
 #pragma unroll
         for (int e = 0; e < DL; ++e) qf[r][e] *= scale;
     }
@@ -145,16 +120,16 @@ __device__ __forceinline__ void decode_attn_chunk(
     const int64_t col = int64_t(g) * D + dl * DL;
     // every key and value slice of the chunk requested before the first score (rows past
     // the chunk read as its last row, then ignored), so the HBM latency is paid once
-    constexpr int NQ = DL * int(sizeof(T)) / 16;      // 16-byte pieces per slice
-    u32x4 kraw[IT][NQ], vraw[IT][NQ];
+    constexpr int NQ = DL / 4;                         // 16-byte pieces per slice
+    f32x4 kraw[IT][NQ], vraw[IT][NQ];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int j = min(j0 + 8 * IT * w + 8 * it + kg, jend - 1);
         const int64_t off = (row0 + j) * ldkv + col;
 #pragma unroll
         for (int c = 0; c < NQ; ++c) {
-            kraw[it][c] = *reinterpret_cast<const u32x4*>(K + off + c * (16 / int(sizeof(T))));
-            vraw[it][c] = *reinterpret_cast<const u32x4*>(V + off + c * (16 / int(sizeof(T))));
+            kraw[it][c] = *reinterpret_cast<const f32x4*>(K + off + 4 * c);
+            vraw[it][c] = *reinterpret_cast<const f32x4*>(V + off + 4 * c);
         }
     }
 #pragma unroll
@@ -165,15 +140,12 @@ __device__ __forceinline__ void decode_attn_chunk(
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int j = j0 + 8 * IT * w + 8 * it + kg;
-        float kf[DL], vf[DL];
-        unpack_slice<T, DL>(kraw[it], kf);
-        unpack_slice<T, DL>(vraw[it], vf);
         const bool ok = j < jend && j < valid;   // padding of the full-batching layout is read, then masked
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float s = 0.f;
 #pragma unroll
-            for (int e = 0; e < DL; ++e) s = fmaf(qf[r][e], kf[e], s);
+            for (int e = 0; e < DL; ++e) s = fmaf(qf[r][e], kraw[it][e / 4][e % 4], s);
             s += __shfl_xor(s, 1);
             s += __shfl_xor(s, 2);
             s += __shfl_xor(s, 4);
@@ -183,7 +155,7 @@ __device__ __forceinline__ void decode_attn_chunk(
                 const float p = exp2f(s - mn);
                 l[r] = l[r] * a + p;
 #pragma unroll
-                for (int e = 0; e < DL; ++e) o[r][e] = fmaf(p, vf[e], o[r][e] * a);
+                for (int e = 0; e < DL; ++e) o[r][e] = fmaf(p, vraw[it][e / 4][e % 4], o[r][e] * a);
                 m[r] = mn;
             }
         }
@@ -430,8 +402,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? (R <= 2 ? 4 : R == 4 ? 3 : 2)
             decode_attn_chunk_bf16<R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
                                       step, Hkv, n_ctx_chunks, n_chunks, part, i, g, c);
         else
-            decode_attn_chunk<T, D, R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
-                                       step, Hkv, n_ctx_chunks, n_chunks, part, i, g, c);
+            decode_attn_chunk_f32<D, R>(q, ldq, ctx_k, ctx_v, gen_k, gen_v, ldkv, ctx_off, ctx_span, ctx_valid, gen_off,
+                                        step, Hkv, n_ctx_chunks, n_chunks, part, i, g, c);
     };
     if (!list) {
         run(blockIdx.x / Hkv, blockIdx.x % Hkv, blockIdx.y);

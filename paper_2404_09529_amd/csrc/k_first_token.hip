@@ -53,11 +53,11 @@ __global__ __launch_bounds__(256) void gather_last_kernel(const float* __restric
 
 // Four wavefronts per workgroup of 128 vocabulary rows: wavefront w owns rows
 // n0 = 128 b + 32 w .. + 31 (two blocks of 16 on the rows of the 16x16x32 bf16 MFMA) and all
-// prompts, 16 MB at a time (MB blocks of 16 on its columns).  K is consumed in chunks of KC
+// prompts, up to 16 MB of them (MB blocks of 16 on its columns).  K is consumed in chunks of KC
 // columns.  A chunk's weight tile (128 rows x 2 KC bytes) and prompt tile (16 MB rows x 2 KC
 // bytes) go from global memory straight into LDS, each 1 KB load a set of whole row segments,
 // through a ring of NCH chunks: NCH - 1 chunks are in flight while one is consumed.  The LM
-// head streams through once per pass of 16 MB prompts; the prompt rows come from L2.  Rows
+// head streams through once; the prompt rows come from L2.  Rows
 // past the vocabulary or the prompts are read as the last row (every load in range) and never
 // reported.  In block (nb, mb) lane l holds the logits of prompt 16 mb + l % 16 for vocabulary
 // rows n0 + 16 nb + 4 (l / 16) + 0..3.
@@ -146,93 +146,90 @@ __global__ __launch_bounds__(256, 1) void lm_head_bf16_kernel(const bf16* __rest
         woff[t] = min(row, last_row) * d * 2 + 16 * (lchk ^ lm_swz<KC>(row));
     }
     const int f_sw = lm_swz<KC>(lr);
-    for (int m0 = 0; m0 < k_pad; m0 += 16 * MB) {
-        const int nmb = min(MB, (k_pad - m0) / 16);
-        const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<bf16*>(hl + int64_t(m0) * d), 0, 16 * nmb * d * 2, kRsrcWord3);
-        int poff[G::P_LD];
+    const int nmb = k_pad / 16;   // prompt blocks, at most MB
+    const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16*>(hl), 0, 16 * nmb * d * 2, kRsrcWord3);
+    int poff[G::P_LD];
 #pragma unroll
-        for (int t = 0; t < G::P_LD; ++t) {
-            const int row = G::RPL * (G::P_LD * wave + t) + lrow;
-            poff[t] = min(row, 16 * nmb - 1) * d * 2 + 16 * (lchk ^ lm_swz<KC>(row));
-        }
-        f32x4 acc[NB][MW] = {};
+    for (int t = 0; t < G::P_LD; ++t) {
+        const int row = G::RPL * (G::P_LD * wave + t) + lrow;
+        poff[t] = min(row, 16 * nmb - 1) * d * 2 + 16 * (lchk ^ lm_swz<KC>(row));
+    }
+    f32x4 acc[NB][MW] = {};
 #pragma unroll
-        for (int c = 0; c < NCH - 1; ++c) lm_issue<G, NCH>(wrs, hrs, smem, c, n_ch, wave, woff, poff);
-        // At the top of chunk c the loads issued after its own are those of chunks c + 1 ..
-        // c + NCH - 2: (NCH - 2) chunks of W_LD + P_LD loads per wavefront.
-        for (int c = 0; c < n_ch; ++c) {
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((NCH - 2) * (G::W_LD + G::P_LD)));
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            // into the slot every wavefront finished at c - 1
-            lm_issue<G, NCH>(wrs, hrs, smem, c + NCH - 1, n_ch, wave, woff, poff);
-            const char* slot = smem + (c % NCH) * G::CH_B;
+    for (int c = 0; c < NCH - 1; ++c) lm_issue<G, NCH>(wrs, hrs, smem, c, n_ch, wave, woff, poff);
+    // At the top of chunk c the loads issued after its own are those of chunks c + 1 ..
+    // c + NCH - 2: (NCH - 2) chunks of W_LD + P_LD loads per wavefront.
+    for (int c = 0; c < n_ch; ++c) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((NCH - 2) * (G::W_LD + G::P_LD)));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        // into the slot every wavefront finished at c - 1
+        lm_issue<G, NCH>(wrs, hrs, smem, c + NCH - 1, n_ch, wave, woff, poff);
+        const char* slot = smem + (c % NCH) * G::CH_B;
 #pragma unroll
-            for (int st = 0; st < KC / 32; ++st) {
-                const int ch = 16 * ((4 * st + q4) ^ f_sw);
-                bf16x8 wf[NB], pf[MW];
+        for (int st = 0; st < KC / 32; ++st) {
+            const int ch = 16 * ((4 * st + q4) ^ f_sw);
+            bf16x8 wf[NB], pf[MW];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                wf[nb] = *reinterpret_cast<const bf16x8*>(slot + (n0 - nb0 + 16 * nb + lr) * G::ROW_B + ch);
+#pragma unroll
+            for (int mb = 0; mb < MW; ++mb)
+                if (MW * wp + mb < nmb)
+                    pf[mb] = *reinterpret_cast<const bf16x8*>(slot + G::W_B + (16 * (MW * wp + mb) + lr) * G::ROW_B + ch);
+#pragma unroll
+            for (int mb = 0; mb < MW; ++mb) {
+                if (MW * wp + mb >= nmb) break;
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-                    wf[nb] = *reinterpret_cast<const bf16x8*>(slot + (n0 - nb0 + 16 * nb + lr) * G::ROW_B + ch);
-#pragma unroll
-                for (int mb = 0; mb < MW; ++mb)
-                    if (MW * wp + mb < nmb)
-                        pf[mb] = *reinterpret_cast<const bf16x8*>(slot + G::W_B + (16 * (MW * wp + mb) + lr) * G::ROW_B + ch);
-#pragma unroll
-                for (int mb = 0; mb < MW; ++mb) {
-                    if (MW * wp + mb >= nmb) break;
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf[mb], acc[nb][mb], 0, 0, 0);
-                }
+                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], pf[mb], acc[nb][mb], 0, 0, 0);
             }
         }
-        // the loads past the last chunk are dead (clamped, never read); none may still be writing
-        // LDS when the ring is refilled or the workgroup ends
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
-        // logits and each lane's best of its 4 NB vocabulary rows, per prompt block
+    }
+    // the loads past the last chunk are dead (clamped, never read); none may still be writing
+    // LDS when the workgroup ends
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+    // logits and each lane's best of its 4 NB vocabulary rows, per prompt block
 #pragma unroll
-        for (int mb = 0; mb < MW; ++mb) {
-            const int gb = MW * wp + mb;
-            if (gb >= nmb) break;
-            const int m = m0 + 16 * gb + lr;
-            float bv = -INFINITY;
-            int bi = INT32_MAX;
+    for (int mb = 0; mb < MW; ++mb) {
+        const int gb = MW * wp + mb;
+        if (gb >= nmb) break;
+        const int m = 16 * gb + lr;
+        float bv = -INFINITY;
+        int bi = INT32_MAX;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int nbase = n0 + 16 * nb + 4 * q4;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int nbase = n0 + 16 * nb + 4 * q4;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (nbase + r >= V) continue;
-                    const float v = acc[nb][mb][r];
-                    if (logits && m < k) logits[int64_t(m) * V + nbase + r] = v;
-                    if (better(v, nbase + r, bv, bi)) { bv = v; bi = nbase + r; }
-                }
+            for (int r = 0; r < 4; ++r) {
+                if (nbase + r >= V) continue;
+                const float v = acc[nb][mb][r];
+                if (logits && m < k) logits[int64_t(m) * V + nbase + r] = v;
+                if (better(v, nbase + r, bv, bi)) { bv = v; bi = nbase + r; }
             }
-            // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same prompt
-#pragma unroll
-            for (int x = 16; x < 64; x <<= 1) {
-                const float ov = __shfl_xor(bv, x);
-                const int oi = __shfl_xor(bi, x);
-                if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-            }
-            if (lane < 16) red[wr][16 * gb + lane] = ArgMax{bv, bi};
         }
-        __syncthreads();
-        // the WR row groups combined for the 16 MB prompts; prompt m's pairs are contiguous
-        if (threadIdx.x < 16 * nmb && m0 + threadIdx.x < k) {
-            ArgMax b = red[0][threadIdx.x];
+        // lanes l, l ^ 16, l ^ 32, l ^ 48 hold the same prompt
 #pragma unroll
-            for (int w2 = 1; w2 < WR; ++w2) {
-                const ArgMax o = red[w2][threadIdx.x];
-                if (better(o.v, o.i, b.v, b.i)) b = o;
-            }
-            part[int64_t(m0 + threadIdx.x) * gridDim.x + blockIdx.x] = b;
+        for (int x = 16; x < 64; x <<= 1) {
+            const float ov = __shfl_xor(bv, x);
+            const int oi = __shfl_xor(bi, x);
+            if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
         }
-        __syncthreads();
+        if (lane < 16) red[wr][16 * gb + lane] = ArgMax{bv, bi};
+    }
+    __syncthreads();
+    // the WR row groups combined for the prompts; prompt m's pairs are contiguous
+    if (threadIdx.x < k) {
+        ArgMax b = red[0][threadIdx.x];
+#pragma unroll
+        for (int w2 = 1; w2 < WR; ++w2) {
+            const ArgMax o = red[w2][threadIdx.x];
+            if (better(o.v, o.i, b.v, b.i)) b = o;
+        }
+        part[int64_t(threadIdx.x) * gridDim.x + blockIdx.x] = b;
     }
 }
 
