@@ -130,11 +130,14 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(const float* __restrict__ 
     }
     constexpr int kSlots = STEPS > 0 ? STEPS : kDepth;
     f32x4 ra[kSlots][2], rb[kSlots][2];
-    auto issue = [&](int u, int s) {   // step s of K into slot u
+    // step s of K into slot u (in range; with the clamp the long form is 2% faster: 4096 x 4096 x 1024
+    // 530 and 518 us)
+    auto issue = [&](int u, int s) {
+        const int k = TK * (STEPS == kLong ? min(s, K / TK - 1) : s);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            ra[u][i] = *reinterpret_cast<const f32x4*>(a[i] + TK * s);
-            rb[u][i] = *reinterpret_cast<const f32x4*>(b[i] + TK * s);
+            ra[u][i] = *reinterpret_cast<const f32x4*>(a[i] + k);
+            rb[u][i] = *reinterpret_cast<const f32x4*>(b[i] + k);
         }
     };
     auto multiply = [&](int u, f32x4 (&acc)[2][2]) {   // [weight block][activation block]
