@@ -10,7 +10,8 @@
 // tiles on all the CUs for a few hundred rows, larger ones as soon as they fill the CUs.
 // Measured (us, 256 x 256 tiles -> the tile chosen): 344 rows, N 2048, K 5504: 109 -> 25 (64 x 64);
 // 344 rows, N 11008, K 2048: 46 -> 33 (128 x 256); 150 rows, N 2048, K 5504: 111 -> 22 (32 x 64);
-// 1309 rows, N 2048, K 5504: 110 -> 47 (128 x 128); 512 rows, N 4096, K 14336: 259 -> 102 (128 x 64).
+// 1309 rows, N 2048, K 5504: 110 -> 47 (128 x 128; 57-59 in an MLP call, whose activations were written
+// just before and whose weights come from HBM); 512 rows, N 4096, K 14336: 259 -> 102 (128 x 64).
 //
 // One 256-thread workgroup (2 x 2 wavefronts) per tile, persistent: a workgroup's tiles form one
 // stream of K-steps through an LDS ring of NS slots (A rows, then B rows of one step), filled

@@ -69,11 +69,11 @@ def _check(lengths, hidden, lm_head, tokens, logits, bf16=True):
 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("case", ["one-prompt", "one-prompt-d512", "ragged-vocab", "ragged-vocab-d512", "33-prompts-d1024",
-                                  "two-prompt-chunks", "two-passes-of-128", "llama2-7b-vocab", "bimodal-96-prompts",
+                                  "two-prompt-chunks", "150-prompts", "llama2-7b-vocab", "bimodal-96-prompts",
                                   "llama3-8b-vocab"])
 def test_first_token_bf16(case):
-    # up to 64 prompts are one pass of 64 (K in segments of 512 columns when d allows); more,
-    # passes of 128 (the last one partial)
+    # up to 64 prompts (K in segments of 512 columns when d allows); more on 128 vocabulary rows a
+    # workgroup or, from 129 prompts at any vocabulary, on the GEMM tiles
     if case in ("llama2-7b-vocab", "bimodal-96-prompts", "llama3-8b-vocab"):
         # full size: the prompts of the Llama-2-7B lognormal (64), bimodal (96) and Llama-3-8B (128)
         # workloads with their vocabularies, d 4096
@@ -85,11 +85,11 @@ def test_first_token_bf16(case):
                    "ragged-vocab-d512": [5, 1, 12, 3, 9],
                    "33-prompts-d1024": list(np.random.default_rng(5).integers(1, 50, 33)),
                    "two-prompt-chunks": list(np.random.default_rng(3).integers(1, 40, 70)),
-                   "two-passes-of-128": list(np.random.default_rng(4).integers(1, 30, 150))}[case]
+                   "150-prompts": list(np.random.default_rng(4).integers(1, 30, 150))}[case]
         V, d = {"one-prompt": (1000, 256), "one-prompt-d512": (129, 512), "ragged-vocab": (1000, 256),
                 "ragged-vocab-d512": (1000, 512),
                 "33-prompts-d1024": (777, 1024), "two-prompt-chunks": (3000, 512),
-                "two-passes-of-128": (2000, 256)}[case]
+                "150-prompts": (2000, 256)}[case]
     rng = np.random.default_rng([len(lengths), V, d])
     hidden = rng.standard_normal((int(np.sum(lengths)), d), dtype=np.float32)   # unit RMS, like a normed state
     lm_head = rand_bf16(rng, (V, d), 0.02)
