@@ -23,7 +23,7 @@ int cu_count();
 
 // Tile sizes (rows x columns) and the measured time in us of a tile's K-step of 64, a CU's tiles
 // one after another (two workgroups of a CU together: per tile).  Each step moves (rows +
-// columns) x 128 bytes into LDS, at about 60 GB/s per CU for all of them.
+// columns) x 128 bytes into LDS, at about 60 GB/s per CU for all of them (weights in the Infinity Cache).
 constexpr int kGemmTiles = 5;
 constexpr int kTileRows[kGemmTiles] = {32, 64, 128, 128, 128};
 constexpr int kTileCols[kGemmTiles] = {64, 64, 64, 128, 256};

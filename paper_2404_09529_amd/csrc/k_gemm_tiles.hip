@@ -3,11 +3,13 @@
 // or too badly divided, for the 256 CUs.
 //
 // What bounds it: each K-step of 64 moves (BM + BN) x 128 bytes into LDS for BM BN 128 flops, and
-// a CU receives about 60 GB/s whatever the tile and the ring depth (8 steps ahead are no faster
-// than 4, and the kernel without its MFMAs takes the same time): the tiles of an XCD walk K
-// together, so every line comes from beyond L2, and a CU's misses in flight over that latency
-// are its rate (lines already in L2 reach it at 120-150 GB/s).  So the time is bytes per CU: small
-// tiles on all the CUs for a few hundred rows, larger ones as soon as they fill the CUs.
+// a CU receives about 60 GB/s with warm weights, 30-50 in a call, whatever the tile and the ring depth (8 steps
+// ahead are no faster than 4, and the kernel without its MFMAs takes the same time); lines that were in
+// L2 before the launch reach it at 120-150 GB/s.  60-84% of its requests hit L2 (counters): an XCD
+// misses a line about once, but its tiles walk K together and ask for the line in the same steps, so
+// the hits seem to wait for that miss, and a CU's requests in flight over that latency to be its rate.
+// So the time is bytes per CU: small tiles on all the CUs for a few hundred rows, larger ones as
+// soon as they fill the CUs.
 // Measured (us, 256 x 256 tiles -> the tile chosen): 344 rows, N 2048, K 5504: 109 -> 25 (64 x 64);
 // 344 rows, N 11008, K 2048: 46 -> 33 (128 x 256); 150 rows, N 2048, K 5504: 111 -> 22 (32 x 64);
 // 1309 rows, N 2048, K 5504: 110 -> 47 (128 x 128; 57-59 in an MLP call, whose activations were written
