@@ -108,23 +108,25 @@ Layout layout_of(const pp_config* c, const pp_gen_dlayout* g) {
     L.q = take(c->dtype == PP_BF16 ? k * hd * 2 : k * qkv_w * 4);   // bf16: rotated queries only
     L.attn = take(k * hd * e);
     L.act = take(k * F * e);
-    const size_t chunk_bytes = k * size_t(c->n_heads) * nch * (D + 4) * 4;
     const Plan plan = plan_of(c, g->k);
+    size_t sums = 0;   // bytes of O's and down's partial sums
     if (plan.split) {
         Proj p[4];
         projections(c, p);
         int splits = plan.o && plan.down ? 0 : tile_splits(g->k);
         if (plan.o) splits = std::max(splits, ppk::skinny_split(p[1].N, p[1].K).splits);
         if (plan.down) splits = std::max(splits, ppk::decode_gemm_splits(g->k, p[3].N, p[3].K));
-        const size_t sums = size_t(splits) * k * d * 4;
-        // a streamed O merges the chunk results while it leaves its sums; else they are merged before
-        L.part = take(plan.o ? chunk_bytes : std::max(chunk_bytes, sums));
-        L.gpart = plan.o ? take(sums) : L.part;
-    } else {
-        L.part = take(chunk_bytes);
+        sums = size_t(splits) * k * d * 4;
     }
+    // A streamed O merges the attention's chunk results while it leaves its sums, which have a region
+    // of their own; else the chunk results are merged before, and the sums take their place and that of
+    // a region of k d floats which the size of a workspace has always held.
+    L.gpart = take(k * d * 4);
+    L.part = take(k * size_t(c->n_heads) * nch * (D + 4) * 4);
+    if (plan.o) L.gpart = take(sums);
+    else if (sums > off - L.gpart) take(sums - (off - L.gpart));
     L.table = take(k * (D / 2) * sizeof(float2));
-    L.ints = take(2 * k * sizeof(int32_t));
+    L.ints = take((4 * k + 1) * sizeof(int32_t));
     L.ft = take(ppk::first_token_workspace(c->dtype, g->k, c->vocab, c->d_model));
     L.total = off;
     return L;
