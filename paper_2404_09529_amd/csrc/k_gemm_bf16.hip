@@ -106,7 +106,7 @@ __device__ __forceinline__ void stage_put(char* stg, int r, int c, int half, bf1
 
 // The epilogue of one wavefront sub-tile (activation rows mb.., weight rows nb0..).  In block
 // (i, j) lane l holds activation row mb + 16 j + l % 16 and the 4 consecutive weight rows
-// nb0 + 16 i + 4 (l / 16) + 0..3.  stg is this wavefront's 8 KB of LDS, free for the duration
+// nb0 + 16 i + 4 (l / 16) + 0..3.  stg is this wavefront's MB KB of LDS, free for the duration
 // of the epilogue.
 template <int EPI, int MB>
 __device__ __forceinline__ void epilogue(f32x4 (&acc)[8][MB], void* __restrict__ Cv, int64_t ldc, int M,
